@@ -18,7 +18,8 @@ LIB = os.path.join(HERE, "libcat.so")
 ROCM = os.environ.get("ROCM_PATH", "/opt/rocm")
 ARCH = "gfx950"
 
-HIP_SOURCES = ["cat_api.hip", "k_cov.hip", "k_transform_quant.hip", "k_w4a4.hip", "k_sqnr.hip"]
+HIP_SOURCES = ["cat_api.hip", "k_cov.hip", "k_transform_quant.hip", "k_w4a4.hip", "k_w4a4_split.hip",
+               "k_sqnr.hip"]
 CXX_SOURCES = ["host_builder.cpp", "errors.cpp"]
 
 HIP_FLAGS = [

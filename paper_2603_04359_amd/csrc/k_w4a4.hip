@@ -467,7 +467,7 @@ __device__ __forceinline__ void gemm_body(
     // group runs its own straight-line loop (same barrier count per tile).
     auto zero_acc = [&]() {
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
+        for (int i = 0; i < IM; ++i)
 #pragma unroll
             for (int j = 0; j < 2; ++j) acc[i][j] = i32x16{};
     };
@@ -549,6 +549,18 @@ __global__ __launch_bounds__(kGemmThreads, kWgPerCu) void w4a4_asym_gemm_kernel(
                            rsum_w, &sasym);
 }
 
+// Estimated clocks of a launch with 128- (small) or 256-token tiles: rounds
+// of the grid, each nk steps and a fixed part (filling the ring, storing the
+// tile).  Measured: at 128 tokens 1680 clocks per step and 19000 on top
+// (4096 -> 4096 and 14336 -> 4096, 34 and 92 us), at 256 tokens 3600 and
+// 18000 (1000 and 8192 tokens through 4096 -> 14336 and 14336 -> 4096); int8
+// 1400 and 14000, 2400 and 14000.
+static int64_t gemm_cost(bool i8, bool small, int64_t tiles, int64_t slots, int64_t d_in) {
+    const int64_t nk = ((i8 ? d_in : d_in / 2) + kKBP - 1) / kKBP;
+    const int64_t step = small ? (i8 ? 1400 : 1700) : (i8 ? 2400 : 3600);
+    return (tiles + slots - 1) / slots * (nk * step + (i8 ? 14000 : 18000));
+}
+
 static hipError_t launch_gemm(bool i8, const uint8_t* codes_x, const float* s_x,
                               const uint8_t* codes_w, const float* s_w, int64_t n, int64_t d_in,
                               int64_t d_out, float* y, int32_t* acc_out, hipStream_t stream,
@@ -566,6 +578,14 @@ static hipError_t launch_gemm(bool i8, const uint8_t* codes_x, const float* s_x,
     // kWgPerCu resident workgroups per CU, a multiple of the XCD count
     const int64_t slots = (static_cast<int64_t>(cus) * kWgPerCu / kXcd) * kXcd;
     const bool small = T256 < slots && (T128 + slots - 1) / slots <= (T256 + slots - 1) / slots;
+    // few tiles: small tiles with the reduction split over a workgroup's
+    // waves, where its estimate is at least an eighth lower (nearer to the line
+    // the two measure alike: 1170 x 5120 -> 5057 takes 49.1 and 49.8 us)
+    int tile = 0;
+    if (split_gemm_cost(i8, n, d_in, d_out, slots, tile) <
+        gemm_cost(i8, small, small ? T128 : T256, slots, d_in) / 8 * 7)
+        return launch_split_gemm(tile, i8, codes_x, s_x, codes_w, s_w, n, d_in, d_out, y, acc_out,
+                                 zmin_x, rsum_w, stream);
     const int64_t T = small ? T128 : T256;
     int64_t grid = slots;
     const int64_t t_pad = ((T + kXcd - 1) / kXcd) * kXcd;

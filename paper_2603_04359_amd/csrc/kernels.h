@@ -66,6 +66,15 @@ hipError_t launch_int8_linear(const int8_t* codes_x, const float* s_x, const int
                               const float* s_w, int64_t n, int64_t d_in, int64_t d_out,
                               float* y, int32_t* acc_out, hipStream_t stream);
 
+// Small-tile GEMM with the reduction split over a workgroup's waves: the
+// estimated clocks of its best tile shape (an index, in `tile`), and its
+// launch (asymmetric when zmin_x is not NULL).
+int64_t split_gemm_cost(bool i8, int64_t n, int64_t d_in, int64_t d_out, int64_t cus, int& tile);
+hipError_t launch_split_gemm(int tile, bool i8, const uint8_t* codes_x, const float* s_x,
+                             const uint8_t* codes_w, const float* s_w, int64_t n, int64_t d_in,
+                             int64_t d_out, float* y, int32_t* acc_out, const float* zmin_x,
+                             const int32_t* rsum_w, hipStream_t stream);
+
 // ---- second moment accumulation
 // Workspace of launch_cov_accumulate on the current device (0 when the
 // configuration runs on kernels that need none).
