@@ -21,8 +21,8 @@
 // stay in registers for at most 4096 tokens and are then added into acc by
 // the tile's owner together with the transpose.
 //
-// fp32 inputs and blocks smaller than 64 use a vector-ALU kernel with the
-// same tiling and flush policy.
+// fp32 inputs and blocks smaller than 64 use cov_f64_kernel: fp64 MFMA, small
+// tiles, a tile's tokens split over the waves of its workgroup.
 #include "device_common.h"
 #include "kernels.h"
 
@@ -210,63 +210,153 @@ __global__ __launch_bounds__(kCovThreads) void cov_mfma_kernel(const uint16_t* _
     }
 }
 
-// ------------------------------------------------------- vector-ALU path
-// 64 x 64 tile, 16 x 16 threads each owning 4 x 4 outputs; 16-token slabs
-// staged in LDS as fp32.  The partial sums are fp64 and reach acc rounded
-// once per flush: with fp32 running sums over thousands of tokens, a column
-// of heavy-tailed values (say Student-t with two degrees of freedom) left
-// its sum of squares about 1e-5 off.
-template <typename XT>
-__global__ __launch_bounds__(kCovThreads) void cov_valu_kernel(const XT* __restrict__ X, int64_t n,
+// ------------------------------------------------------------- fp64 path
+// fp32 operands, and bf16 blocks the paths above do not take.  One workgroup
+// of 8 waves per 16 NT x 16 NT upper-triangle tile; wave w multiplies the
+// 4-token groups w, w + 8, ... with v_mfma_f64_16x16x4_f64, and the waves'
+// partial sums meet in LDS in wave order.  The sums are fp64 and reach acc
+// rounded once per flush: with fp32 running sums over thousands of tokens, a
+// column of heavy-tailed values (say Student-t with two degrees of freedom)
+// left its sum of squares about 1e-5 off.
+//
+// The operands need no LDS: a fragment is 4 token rows of 16 channels, read
+// from global memory.  With VEC a lane reads NT consecutive channels at once
+// and fragment a is channels a, NT + a, 2 NT + a, ... of the tile (the vector
+// memory path takes about as long for a 4-byte load as for a 16-byte one, and
+// bounds the small tiles); without it, channels 16 a ... 16 a + 15.  Small
+// problems are bound by latency, so the launcher takes the largest tile that
+// still gives half the CUs one: 512 tokens of 8 blocks of 32 channels took 66
+// us as 8 workgroups of 64 x 64 vector-ALU tiles walking all tokens and take
+// under 9 us; 2048 x 512, whole matrix, 368 us and 27 us; 8192 x 1024 1527 us
+// and 275 us.
+typedef double f64x4 __attribute__((ext_vector_type(4)));
+constexpr int kCovFWaves = 8;
+constexpr int kCovFThreads = kCovFWaves * kWave;
+
+// NT consecutive elements at p (aligned to their size) as fp32.
+template <int NT>
+__device__ __forceinline__ void cov_load_vec(const float* p, float (&v)[NT]) {
+    typedef float vec __attribute__((ext_vector_type(NT)));
+    const vec x = *reinterpret_cast<const vec*>(p);
+#pragma unroll
+    for (int a = 0; a < NT; ++a) v[a] = x[a];
+}
+template <int NT>
+__device__ __forceinline__ void cov_load_vec(const uint16_t* p, float (&v)[NT]) {
+    typedef uint16_t vec __attribute__((ext_vector_type(NT)));
+    const vec x = *reinterpret_cast<const vec*>(p);
+#pragma unroll
+    for (int a = 0; a < NT; ++a) v[a] = bf16_bits_to_f32(x[a]);
+}
+
+template <typename XT, int NT, bool VEC>
+__global__ __launch_bounds__(kCovFThreads) void cov_f64_kernel(const XT* __restrict__ X, int64_t n,
                                                                int64_t d, int mode, int64_t k,
                                                                float* __restrict__ acc) {
-    constexpr int TILE = 64, TKV = 16;
-    __shared__ float xa[TKV][TILE];
-    __shared__ float xb[TKV][TILE];
+    constexpr int TILE = 16 * NT;
+    constexpr int UN = NT == 4 ? 4 : 8;             // 4-token groups in flight per wave
+    constexpr int kStep = UN * kCovFWaves;          // groups per round of the 8 waves
+    __shared__ f64x4 red[kCovFWaves][NT * kWave];
     const CovTile ct = cov_tile(blockIdx.x, TILE, d, mode, k);
     const bool diag = ct.I0 == ct.J0;
-    const int ti = threadIdx.x / 16, tj = threadIdx.x % 16;
+    const int tid = threadIdx.x;
+    const int lane = tid & (kWave - 1), wave = tid / kWave;
+    const int l16 = lane & 15, q4 = lane >> 4;
+    // channel of fragment a, lane or row i, inside the tile
+    auto chan = [](int a, int i) { return VEC ? NT * i + a : 16 * a + i; };
+    // channels past the matrix read a valid one (their results are not stored)
+    int64_t ca[NT], cb[NT];
+#pragma unroll
+    for (int a = 0; a < NT; ++a) {
+        const int64_t ci = ct.I0 + chan(a, l16), cj = ct.J0 + chan(a, l16);
+        ca[a] = ct.colbase + (ci < ct.dim ? ci : 0);
+        cb[a] = ct.colbase + (cj < ct.dim ? cj : 0);
+    }
+    auto load = [&](const XT* row, float (&xa)[NT], float (&xb)[NT]) {
+        if constexpr (VEC) {
+            cov_load_vec<NT>(row + ca[0], xa);
+            cov_load_vec<NT>(row + cb[0], xb);
+        } else {
+#pragma unroll
+            for (int a = 0; a < NT; ++a) {
+                xa[a] = load_as_f32(row, ca[a]);
+                xb[a] = load_as_f32(row, cb[a]);
+            }
+        }
+    };
     for (int64_t f0 = 0; f0 < n; f0 += kCovFlush) {
         const int64_t f1 = f0 + kCovFlush < n ? f0 + kCovFlush : n;
-        double part[4][4] = {};
-        for (int64_t t0 = f0; t0 < f1; t0 += TKV) {
-            for (int e = threadIdx.x; e < TKV * TILE; e += kCovThreads) {
-                const int tt = e / TILE, c = e % TILE;
-                const int64_t t = t0 + tt;
-                const int64_t ci = ct.I0 + c, cj = ct.J0 + c;
-                xa[tt][c] = (t < f1 && ci < ct.dim) ? load_as_f32(X, t * d + ct.colbase + ci) : 0.f;
-                xb[tt][c] = (t < f1 && cj < ct.dim) ? load_as_f32(X, t * d + ct.colbase + cj) : 0.f;
-            }
-            __syncthreads();
-            for (int tt = 0; tt < TKV; ++tt) {
-                float a[4], b[4];
+        f64x4 part[NT][NT];
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    a[q] = xa[tt][4 * ti + q];
-                    b[q] = xb[tt][4 * tj + q];
-                }
+        for (int a = 0; a < NT; ++a)
 #pragma unroll
-                for (int p = 0; p < 4; ++p)
+            for (int b = 0; b < NT; ++b) part[a][b] = f64x4{0.0, 0.0, 0.0, 0.0};
+        auto products = [&](const float (&xa)[UN][NT], const float (&xb)[UN][NT]) {
 #pragma unroll
-                    for (int q = 0; q < 4; ++q)
-                        part[p][q] = fma(static_cast<double>(a[p]), static_cast<double>(b[q]),
-                                         part[p][q]);
-            }
-            __syncthreads();
+            for (int u = 0; u < UN; ++u)
+#pragma unroll
+                for (int a = 0; a < NT; ++a)
+#pragma unroll
+                    for (int b = 0; b < NT; ++b)
+                        part[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(
+                            static_cast<double>(xa[u][a]), static_cast<double>(xb[u][b]), part[a][b], 0, 0, 0);
+        };
+        int64_t t = f0 + 4 * wave + q4;              // this lane's token of the wave's first group
+        const int64_t full = f0 + (f1 - f0) / (4 * kStep) * (4 * kStep);   // whole rounds end here
+        for (; t < full; t += 4 * kStep) {
+            float xa[UN][NT], xb[UN][NT];
+            const XT* row = X + t * d;
+#pragma unroll
+            for (int u = 0; u < UN; ++u) load(row + u * (4 * kCovFWaves) * d, xa[u], xb[u]);
+            products(xa, xb);
         }
+        if (full < f1) {
+            // the last, ragged round: tokens past the end are zeros
+            float xa[UN][NT], xb[UN][NT];
 #pragma unroll
-        for (int p = 0; p < 4; ++p)
+            for (int u = 0; u < UN; ++u) {
+                const int64_t tu = t + u * (4 * kCovFWaves);
+                const bool live = tu < f1;
+                load(X + (live ? tu : f0) * d, xa[u], xb[u]);
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int64_t gi = ct.I0 + 4 * ti + p, gj = ct.J0 + 4 * tj + q;
-                if (gi >= ct.dim || gj >= ct.dim) continue;
-                float* ptr = acc + ct.base + gi * ct.dim + gj;
-                *ptr = static_cast<float>(*ptr + part[p][q]);
-                if (!diag) {
-                    float* m = acc + ct.base + gj * ct.dim + gi;
-                    *m = static_cast<float>(*m + part[p][q]);
+                for (int a = 0; a < NT; ++a) {
+                    xa[u][a] = live ? xa[u][a] : 0.0f;
+                    xb[u][a] = live ? xb[u][a] : 0.0f;
                 }
             }
+            products(xa, xb);
+        }
+        // owner flush: acc += sums (and the transpose off the diagonal), one
+        // row of fragments at a time; a lane's four values are rows q4, q4 +
+        // 4, q4 + 8, q4 + 12 of column l16
+#pragma unroll
+        for (int a = 0; a < NT; ++a) {
+            __syncthreads();
+#pragma unroll
+            for (int b = 0; b < NT; ++b) red[wave][b * kWave + lane] = part[a][b];
+            __syncthreads();
+            if (tid < NT * kWave) {
+                f64x4 v = red[0][tid];
+#pragma unroll
+                for (int w = 1; w < kCovFWaves; ++w) {
+                    const f64x4 p = red[w][tid];
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) v[r] += p[r];
+                }
+                const int64_t gj = ct.J0 + chan(wave, l16);     // tid / 64: the column fragment
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const int64_t gi = ct.I0 + chan(a, 4 * r + q4);
+                    if (gi >= ct.dim || gj >= ct.dim) continue;
+                    float* ptr = acc + ct.base + gi * ct.dim + gj;
+                    *ptr = static_cast<float>(*ptr + v[r]);
+                    if (!diag) {
+                        float* m = acc + ct.base + gj * ct.dim + gi;
+                        *m = static_cast<float>(*m + v[r]);
+                    }
+                }
+            }
+        }
     }
 }
 
@@ -819,6 +909,34 @@ static int64_t cov_grid(int tile, int64_t d, int mode, int64_t k) {
     return (d / k) * (T * (T + 1) / 2);
 }
 
+template <typename XT, int NT>
+static hipError_t launch_cov_f64_tile(const XT* X, int64_t n, int64_t d, int mode, int64_t k,
+                                      float* acc, hipStream_t stream) {
+    const dim3 g(static_cast<uint32_t>(cov_grid(16 * NT, d, mode, k))), blk(kCovFThreads);
+    // NT channels at once where every row and matrix starts on a whole vector
+    const int64_t dim = mode == CAT_COV_FULL ? d : k;
+    if (NT > 1 && d % NT == 0 && dim % NT == 0)
+        hipLaunchKernelGGL((cov_f64_kernel<XT, NT, (NT > 1)>), g, blk, 0, stream, X, n, d, mode, k, acc);
+    else
+        hipLaunchKernelGGL((cov_f64_kernel<XT, NT, false>), g, blk, 0, stream, X, n, d, mode, k, acc);
+    return hipGetLastError();
+}
+
+template <typename XT>
+static hipError_t launch_cov_f64(const XT* X, int64_t n, int64_t d, int mode, int64_t k, float* acc,
+                                 hipStream_t stream) {
+    int cus = 0;
+    const hipError_t err = device_cus(cus);
+    if (err != hipSuccess) return err;
+    // the largest tile (fewest reads per product) that gives half the CUs one
+    const int64_t dim = mode == CAT_COV_FULL ? d : k;
+    if (2 * cov_grid(64, d, mode, k) >= cus && dim > 32)
+        return launch_cov_f64_tile<XT, 4>(X, n, d, mode, k, acc, stream);
+    if (2 * cov_grid(32, d, mode, k) >= cus && dim > 16)
+        return launch_cov_f64_tile<XT, 2>(X, n, d, mode, k, acc, stream);
+    return launch_cov_f64_tile<XT, 1>(X, n, d, mode, k, acc, stream);
+}
+
 hipError_t launch_cov_accumulate(const void* X, int x_bf16, int64_t n, int64_t d, int mode,
                                  int64_t k, float* acc, void* workspace, size_t workspace_bytes,
                                  hipStream_t stream) {
@@ -864,16 +982,8 @@ hipError_t launch_cov_accumulate(const void* X, int x_bf16, int64_t n, int64_t d
         }
         return hipGetLastError();
     }
-    const int64_t g = cov_grid(64, d, mode, k);
-    if (x_bf16)
-        hipLaunchKernelGGL(cov_valu_kernel<uint16_t>, dim3(static_cast<uint32_t>(g)),
-                           dim3(kCovThreads), 0, stream, static_cast<const uint16_t*>(X), n, d,
-                           mode, k, acc);
-    else
-        hipLaunchKernelGGL(cov_valu_kernel<float>, dim3(static_cast<uint32_t>(g)),
-                           dim3(kCovThreads), 0, stream, static_cast<const float*>(X), n, d, mode,
-                           k, acc);
-    return hipGetLastError();
+    if (x_bf16) return launch_cov_f64(static_cast<const uint16_t*>(X), n, d, mode, k, acc, stream);
+    return launch_cov_f64(static_cast<const float*>(X), n, d, mode, k, acc, stream);
 }
 
 }  // namespace catk

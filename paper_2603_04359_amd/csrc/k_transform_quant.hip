@@ -16,7 +16,7 @@
 //   single pass     (bf16, k = 128, d = 2048, 4096, 8192; tq_fused_kernel)
 //                   one launch reads X once; workgroups exchange per-token
 //                   block maxima through the workspace in two levels;
-//   two passes      (every other case) run over the same tiles:
+//   two passes      (most other cases) run over the same tiles:
 //     pass 1 (amax) computes z and folds max|z| into a per-token word
 //                   (LDS atomics, then one atomic max per token on the
 //                   float's bit pattern: all values are non-negative, so
@@ -24,13 +24,16 @@
 //     pass 2 (quant) recomputes z with the identical instruction sequence,
 //                   reads the finished row maximum and writes packed codes.
 //   A fill kernel clears the per-token words first (no hipMemset, so the
-//   sequence can be captured in a graph).
+//   sequence can be captured in a graph);
+//   whole rows      (fp32 operands and other bf16 blocks of at least 16,
+//                   d <= 4096; tq_rows_kernel) one launch, a workgroup holds
+//                   the whole rows of 16 tokens.
 // Two-pass kernels, by case: tq_group_kernel (bf16, k <= 256, d a multiple
 // of 256), tq_ring_kernel (bf16 k = 512, and k = 128 or 256 otherwise),
-// tq_mfma_kernel (bf16 k = 32, 64 otherwise) and the vector-ALU kernels
-// (fp32 operands or other block sizes).  The asymmetric INT4 variant takes
-// the same routes with a row maximum and minimum, except that bf16 k = 32
-// and 64 off the group kernel's widths go to the vector ALU.
+// tq_mfma_kernel (bf16 k = 32, 64 otherwise) and the vector-ALU kernels (the
+// rest).  The asymmetric INT4 variant takes the same routes with a row maximum
+// and minimum, except that bf16 k = 32 and 64 off the group kernel's widths go
+// to whole rows or the vector ALU.
 //
 // bf16 kernels run v_mfma_f32_32x32x16_bf16 with A = rows of T_b and B =
 // token rows of X, so Z^T tiles come out with one token per lane column;
@@ -51,6 +54,12 @@ constexpr int64_t kTqTargetWorkgroups = 512;
 __global__ void fill_zero_u32_kernel(uint32_t* p, int64_t n) {
     const int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
     if (i < n) p[i] = 0u;
+}
+// The two-pass paths clear their per-token words first.
+static hipError_t launch_fill_zero(uint32_t* p, int64_t n, hipStream_t stream) {
+    hipLaunchKernelGGL(fill_zero_u32_kernel, dim3(static_cast<uint32_t>((n + 255) / 256)), dim3(256),
+                       0, stream, p, n);
+    return hipGetLastError();
 }
 
 // Quantize one value given inv = qmax/amax (amax > 0); returns the code
@@ -95,7 +104,7 @@ __device__ __forceinline__ void asym_scale(uint32_t kmax, uint32_t kmin_c, float
 }
 
 // ------------------------------------------------------------ generic path
-// Vector ALU, for fp32 operands and blocks the MFMA kernels do not take.
+// Vector ALU, for operands and blocks the other kernels do not take.
 // z is summed in fp64 and rounded to fp32 once, so it is fl32 of the exact
 // block product up to a rare double rounding: with fp32 sums a block whose
 // terms cancel heavily can move a code across a rounding boundary, and at
@@ -190,6 +199,159 @@ __global__ __launch_bounds__(kTqThreads) void tq_generic_quant_asym_kernel(
     const int q0 = asym_code(tq_dot(X, T, t, d, k, 2 * cp), zmin, inv);
     const int q1 = asym_code(tq_dot(X, T, t, d, k, 2 * cp + 1), zmin, inv);
     codes[t * pairs + cp] = static_cast<uint8_t>((q0 & 0xF) | ((q1 & 0xF) << 4));
+}
+
+// ---------------------------------------------------------- whole rows
+// fp32 operands (and bf16 blocks the bf16 MFMA kernels do not take), k >= 16,
+// d <= 4096: one workgroup of 16 waves computes whole rows of z for 16 tokens,
+// keeps them in registers across the row maximum and writes the codes, in one
+// launch and one pass (the two-pass kernels above compute z twice, and their
+// per-token atomics from every channel pair queue up: 512 x 256, k = 32 took
+// 62 us in three launches and takes under 9 us here; 2048 x 1024, k = 128 took
+// 2010 us and takes 32 us).  Bound by the fp64 MFMA rate.
+//
+// z is the fp64 sum rounded once, as above, on v_mfma_f64_16x16x4_f64 with A =
+// 16 rows of T and B = 16 token rows.  A lane reads 4 consecutive elements of
+// its row (lane % 16) at 4 (lane / 16) of every 16, and step s of four takes
+// element s: both operands permute the reduction index alike.  MFMA row i is
+// channel 4 (i % 4) + i / 4 of its 16, so that a lane ends up with 4
+// consecutive channels of one token (accumulator r of lane group q is MFMA
+// row 4 r + q).
+typedef double f64x4 __attribute__((ext_vector_type(4)));
+constexpr int kTrWaves = 16;
+constexpr int kTrThreads = kTrWaves * kWave;
+constexpr int kTrTokens = 16;
+constexpr int kTrMaxTiles = 16;                                 // 16-channel tiles per wave
+constexpr int64_t kTrMaxD = 16 * kTrWaves * kTrMaxTiles;        // 4096
+
+__device__ __forceinline__ f32x4 load4_as_f32(const float* p) {
+    return *reinterpret_cast<const f32x4*>(p);
+}
+__device__ __forceinline__ f32x4 load4_as_f32(const uint16_t* p) {
+    const u32x2 v = *reinterpret_cast<const u32x2*>(p);
+    return f32x4{__uint_as_float(v[0] << 16), __uint_as_float(v[0] & 0xFFFF0000u),
+                 __uint_as_float(v[1] << 16), __uint_as_float(v[1] & 0xFFFF0000u)};
+}
+
+template <typename XT, typename TT, int QM, bool ASYM, int NTW>
+__global__ __launch_bounds__(kTrThreads) void tq_rows_kernel(
+    const XT* __restrict__ X, const TT* __restrict__ T, int64_t n, int64_t d, int k,
+    uint8_t* __restrict__ codes, float* __restrict__ s_x, float* __restrict__ zmin_x) {
+    static_assert(!ASYM || QM == 7, "asymmetric codes are INT4");
+    __shared__ uint32_t red[ASYM ? 2 : 1][kTrWaves][kTrTokens];
+    const int lane = threadIdx.x & (kWave - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const int l16 = lane & 15, q4 = lane >> 4;
+    const int64_t t = static_cast<int64_t>(blockIdx.x) * kTrTokens + l16;
+    const bool valid = t < n;
+    const XT* xrow = X + (valid ? t : n - 1) * d;
+    const int ntiles = static_cast<int>(d / 16);
+    const int ch = 4 * (l16 & 3) + (l16 >> 2);      // this lane's row of T within a tile
+
+    f32x4 z[NTW];
+    uint32_t mx = 0, mn = 0;
+#pragma unroll
+    for (int i = 0; i < NTW; ++i) {
+        const int tile = i * kTrWaves + wave;
+        z[i] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+        if (tile >= ntiles) continue;
+        const int c0 = 16 * tile;
+        const TT* tr = T + static_cast<int64_t>(c0 + ch) * k + 4 * q4;
+        const XT* xr = xrow + (c0 & ~(k - 1)) + 4 * q4;
+        f64x4 acc = {0.0, 0.0, 0.0, 0.0};
+        // groups of 16 elements: all loads of 4 in flight, then their products
+        auto product = [&](const f32x4& a, const f32x4& b) {
+#pragma unroll
+            for (int s = 0; s < 4; ++s)
+                acc = __builtin_amdgcn_mfma_f64_16x16x4f64(static_cast<double>(a[s]),
+                                                           static_cast<double>(b[s]), acc, 0, 0, 0);
+        };
+        int e = 0;
+        for (; e + 64 <= k; e += 64) {
+            f32x4 a[4], b[4];
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+                a[g] = load4_as_f32(tr + e + 16 * g);
+                b[g] = load4_as_f32(xr + e + 16 * g);
+            }
+#pragma unroll
+            for (int g = 0; g < 4; ++g) product(a[g], b[g]);
+        }
+        for (; e < k; e += 16) product(load4_as_f32(tr + e), load4_as_f32(xr + e));
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            z[i][r] = static_cast<float>(acc[r]);
+            if constexpr (ASYM) {
+                const uint32_t key = fkey(z[i][r]);
+                mx = max(mx, key);
+                mn = max(mn, ~key);
+            } else {
+                mx = max(mx, abs_bits(z[i][r]));
+            }
+        }
+    }
+#pragma unroll
+    for (int x = 16; x < kWave; x <<= 1) {
+        mx = max(mx, static_cast<uint32_t>(__shfl_xor(static_cast<int>(mx), x)));
+        if constexpr (ASYM) mn = max(mn, static_cast<uint32_t>(__shfl_xor(static_cast<int>(mn), x)));
+    }
+    if (q4 == 0) {
+        red[0][wave][l16] = mx;
+        if constexpr (ASYM) red[1][wave][l16] = mn;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < kTrWaves; ++w) {
+        mx = max(mx, red[0][w][l16]);
+        if constexpr (ASYM) mn = max(mn, red[1][w][l16]);
+    }
+    float zmin = 0.0f, s = 0.0f, inv = 0.0f;
+    bool nz = true;
+    if constexpr (ASYM) {
+        asym_scale(mx, mn, zmin, s, inv);
+    } else {
+        constexpr float qmax = static_cast<float>(QM);
+        const float amax = __uint_as_float(mx);
+        s = __fdiv_rn(amax, qmax);
+        nz = amax > 0.0f;
+        inv = nz ? __fdiv_rn(qmax, amax) : 0.0f;
+    }
+    if (valid && wave == 0 && q4 == 0) {
+        s_x[t] = s;
+        if constexpr (ASYM) zmin_x[t] = zmin;
+    }
+#pragma unroll
+    for (int i = 0; i < NTW; ++i) {
+        const int tile = i * kTrWaves + wave;
+        if (tile >= ntiles || !valid) continue;
+        uint32_t p = 0;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int c = ASYM ? asym_code(z[i][r], zmin, inv) : (nz ? quant_code<QM>(z[i][r], inv) : 0);
+            p |= QM == 7 ? static_cast<uint32_t>(c & 0xF) << (4 * r) : static_cast<uint32_t>(c & 0xFF) << (8 * r);
+        }
+        const int64_t c = 16 * tile + 4 * q4;
+        if constexpr (QM == 7)
+            *reinterpret_cast<uint16_t*>(codes + t * (d / 2) + c / 2) = static_cast<uint16_t>(p);
+        else
+            *reinterpret_cast<uint32_t*>(codes + t * d + c) = p;
+    }
+}
+
+static bool tq_rows_fits(int64_t d, int64_t k) { return k >= 16 && d <= kTrMaxD; }
+
+template <int QM, bool ASYM, typename XT, typename TT>
+static hipError_t launch_tq_rows(const XT* X, int64_t n, int64_t d, const TT* T, int64_t k,
+                                 uint8_t* codes, float* s_x, float* zmin_x, hipStream_t stream) {
+    const dim3 grid(static_cast<uint32_t>((n + kTrTokens - 1) / kTrTokens)), block(kTrThreads);
+    // tiles per wave held in registers
+    if (d <= 16 * kTrWaves * 4)
+        hipLaunchKernelGGL((tq_rows_kernel<XT, TT, QM, ASYM, 4>), grid, block, 0, stream, X, T, n, d,
+                           static_cast<int>(k), codes, s_x, zmin_x);
+    else
+        hipLaunchKernelGGL((tq_rows_kernel<XT, TT, QM, ASYM, kTrMaxTiles>), grid, block, 0, stream, X,
+                           T, n, d, static_cast<int>(k), codes, s_x, zmin_x);
+    return hipGetLastError();
 }
 
 // --------------------------------------------------------------- MFMA path
@@ -357,9 +519,11 @@ hipError_t launch_tq_mfma(const uint16_t* X, int64_t n, int64_t d, const uint16_
     if (R > tiles) R = tiles;
     if (R < 1) R = 1;
     const int64_t grid = nbj * R;
+    hipError_t err = launch_fill_zero(ws, n, stream);
+    if (err != hipSuccess) return err;
     hipLaunchKernelGGL((tq_mfma_kernel<K, JC, false, 7>), dim3(static_cast<uint32_t>(grid)),
                        dim3(kTqThreads), 0, stream, X, T, n, d, R, ws, codes, s_x);
-    hipError_t err = hipGetLastError();
+    err = hipGetLastError();
     if (err != hipSuccess) return err;
     hipLaunchKernelGGL((tq_mfma_kernel<K, JC, true, QM>), dim3(static_cast<uint32_t>(grid)),
                        dim3(kTqThreads), 0, stream, X, T, n, d, R, ws, codes, s_x);
@@ -1499,6 +1663,8 @@ hipError_t launch_tq_group(const uint16_t* X, int64_t n, int64_t d, const uint16
     if (R > ntiles) R = ntiles;
     if (R < 1) R = 1;
     const dim3 grid(static_cast<uint32_t>(ngroups * R)), block(kTgThreads);
+    err = launch_fill_zero(ws, ASYM ? 2 * n : n, stream);
+    if (err != hipSuccess) return err;
     hipLaunchKernelGGL((tq_group_kernel<K, false, 7, ASYM>), grid, block, 0, stream, X, T, n, d, R,
                        ws, codes, s_x, zmin_x);
     err = hipGetLastError();
@@ -1541,6 +1707,8 @@ hipError_t launch_tq_ring(const uint16_t* X, int64_t n, int64_t d, const uint16_
     if (err != hipSuccess) return err;
     int64_t R = 0;
     const int64_t grid = tq_ring_grid<K>(n, d, cus, R);
+    err = launch_fill_zero(ws, ASYM ? 2 * n : n, stream);
+    if (err != hipSuccess) return err;
     hipLaunchKernelGGL((tq_ring_kernel<K, false, 7, ASYM>), dim3(static_cast<uint32_t>(grid)),
                        dim3(kTqThreads), 0, stream, X, T, n, d, R, ws, codes, s_x, zmin_x);
     err = hipGetLastError();
@@ -1679,11 +1847,15 @@ hipError_t launch_tq_fused(const uint16_t* X, int64_t n, int64_t d, const uint16
 template <int QM, typename XT, typename TT>
 hipError_t launch_tq_generic(const XT* X, int64_t n, int64_t d, const TT* T, int64_t k,
                              uint8_t* codes, float* s_x, uint32_t* ws, hipStream_t stream) {
+    if (tq_rows_fits(d, k))
+        return launch_tq_rows<QM, false>(X, n, d, T, k, codes, s_x, nullptr, stream);
+    hipError_t err = launch_fill_zero(ws, n, stream);
+    if (err != hipSuccess) return err;
     const int64_t units = n * (d / 2);
     const int64_t grid = (units + kTqThreads - 1) / kTqThreads;
     hipLaunchKernelGGL((tq_generic_amax_kernel<XT, TT>), dim3(static_cast<uint32_t>(grid)),
                        dim3(kTqThreads), 0, stream, X, T, n, d, k, ws);
-    hipError_t err = hipGetLastError();
+    err = hipGetLastError();
     if (err != hipSuccess) return err;
     hipLaunchKernelGGL((tq_generic_quant_kernel<XT, TT, QM>), dim3(static_cast<uint32_t>(grid)),
                        dim3(kTqThreads), 0, stream, X, T, n, d, k, ws, codes, s_x);
@@ -1704,10 +1876,6 @@ static hipError_t launch_tq_qm(const void* X, int x_bf16, int64_t n, int64_t d, 
     }
     amax_ws = reinterpret_cast<uint32_t*>(reinterpret_cast<uint8_t*>(amax_ws) +
                                           tq_twopass_offset(n, d));
-    hipLaunchKernelGGL(fill_zero_u32_kernel, dim3(static_cast<uint32_t>((n + 255) / 256)),
-                       dim3(256), 0, stream, amax_ws, n);
-    hipError_t err = hipGetLastError();
-    if (err != hipSuccess) return err;
     if (x_bf16 && t_bf16 && tq_group_fits(d, k)) {
         const uint16_t* Xb = static_cast<const uint16_t*>(X);
         const uint16_t* Tb = static_cast<const uint16_t*>(T);
@@ -1761,11 +1929,15 @@ template <typename XT, typename TT>
 static hipError_t launch_tq_generic_asym(const XT* X, int64_t n, int64_t d, const TT* T,
                                          int64_t k, uint8_t* codes, float* s_x, float* zmin_x,
                                          uint32_t* ws, hipStream_t stream) {
+    if (tq_rows_fits(d, k))
+        return launch_tq_rows<7, true>(X, n, d, T, k, codes, s_x, zmin_x, stream);
+    hipError_t err = launch_fill_zero(ws, 2 * n, stream);
+    if (err != hipSuccess) return err;
     const int64_t units = n * (d / 2);
     const int64_t grid = (units + kTqThreads - 1) / kTqThreads;
     hipLaunchKernelGGL((tq_generic_minmax_kernel<XT, TT>), dim3(static_cast<uint32_t>(grid)),
                        dim3(kTqThreads), 0, stream, X, T, n, d, k, ws);
-    hipError_t err = hipGetLastError();
+    err = hipGetLastError();
     if (err != hipSuccess) return err;
     hipLaunchKernelGGL((tq_generic_quant_asym_kernel<XT, TT>), dim3(static_cast<uint32_t>(grid)),
                        dim3(kTqThreads), 0, stream, X, T, n, d, k, ws, codes, s_x, zmin_x);
@@ -1789,10 +1961,6 @@ hipError_t launch_transform_quant_asym(const void* X, int x_bf16, int64_t n, int
         if (e != hipSuccess || launched) return e;
     }
     ws = reinterpret_cast<uint32_t*>(reinterpret_cast<uint8_t*>(ws) + tq_twopass_offset(n, d));
-    hipLaunchKernelGGL(fill_zero_u32_kernel, dim3(static_cast<uint32_t>((2 * n + 255) / 256)),
-                       dim3(256), 0, stream, ws, 2 * n);
-    hipError_t err = hipGetLastError();
-    if (err != hipSuccess) return err;
     if (x_bf16 && t_bf16 && tq_group_fits(d, k)) {
         const uint16_t* Xb = static_cast<const uint16_t*>(X);
         const uint16_t* Tb = static_cast<const uint16_t*>(T);
