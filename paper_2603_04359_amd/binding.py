@@ -152,12 +152,32 @@ def _check(fn: str, rc: int):
 
 
 # ------------------------------------------------------------ marshalling
+_torch_module = None
+_Tensor = None
+_raw_stream = None      # torch's raw current-stream query, where this torch has one
+_current_device = None
+
+
 def _torch():
-    import torch
-    return torch
+    global _torch_module, _Tensor, _raw_stream, _current_device
+    if _torch_module is None:
+        import torch
+        _Tensor = torch.Tensor
+        raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+        dev = getattr(torch._C, "_cuda_getDevice", None)
+        if raw is not None and dev is not None:
+            _raw_stream, _current_device = raw, dev
+        _torch_module = torch
+    return _torch_module
 
 
 def _dev_ptr(t, name, dtypes=None, allow_none=False):
+    # A decode step's kernels run for a few microseconds, so the marshalling
+    # is what a small call costs: the passing case takes four attribute reads
+    # (0.3 us a tensor, 0.6 through the full checks below), and anything else
+    # goes through the checks one by one for its error.
+    if type(t) is _Tensor and t.is_cuda and t.is_contiguous() and (dtypes is None or t.dtype in dtypes):
+        return t.data_ptr()
     if t is None:
         if allow_none:
             return None
@@ -203,9 +223,14 @@ def _dtype_code(t):
 
 
 def _stream_ptr(stream):
+    if stream is not None:
+        return stream.cuda_stream
     torch = _torch()
-    s = torch.cuda.current_stream() if stream is None else stream
-    return s.cuda_stream
+    # the same handle as torch.cuda.current_stream().cuda_stream, without a
+    # Stream object per call (0.2 us against 2.9)
+    if _raw_stream is not None and torch.cuda.is_initialized():
+        return _raw_stream(_current_device())
+    return torch.cuda.current_stream().cuda_stream
 
 
 # ------------------------------------------------------------ device calls
