@@ -41,6 +41,7 @@
 // kernel keeps its operands (registers, LDS, DMA rings) is stated at it.
 #include <atomic>
 #include <type_traits>
+#include <utility>
 
 #include "device_common.h"
 #include "kernels.h"
@@ -2008,15 +2009,43 @@ constexpr int legendre13(int a) {
     a = ((a % 13) + 13) % 13;
     return a == 0 ? 0 : (a == 1 || a == 3 || a == 4 || a == 9 || a == 10 || a == 12) ? 1 : -1;
 }
-constexpr int paley28(int r, int c) {
-    const int i = r / 2, j = c / 2, ri = r % 2, cj = c % 2;
-    const int conf = (i == 0 && j == 0) ? 0 : (i == 0 || j == 0) ? 1 : legendre13((i - 1) - (j - 1));
-    const int a = (ri == 1 && cj == 1) ? -1 : 1;                 // [[1, 1], [1, -1]]
-    const int bb = (ri == 0 && cj == 0) ? 1 : -1;                // [[1, -1], [-1, -1]]
-    return conf * a + (i == j ? bb : 0);
+constexpr int conference14(int i, int j) {
+    return (i == 0 && j == 0) ? 0 : (i == 0 || j == 0) ? 1 : legendre13((i - 1) - (j - 1));
+}
+// Row I of C times s, the signs compile-time constants.
+template <int I, int... J>
+__device__ __forceinline__ float conference_row(const float (&s)[14], std::integer_sequence<int, J...>) {
+    float acc = 0.0f;
+    auto term = [&](auto j) {
+        constexpr int c = conference14(I, decltype(j)::value);
+        if constexpr (c > 0) acc = acc + s[decltype(j)::value];
+        else if constexpr (c < 0) acc = acc - s[decltype(j)::value];
+    };
+    (term(std::integral_constant<int, J>{}), ...);
+    return acc;
+}
+template <int... I>
+__device__ __forceinline__ void hadamard28_rows(float (&v)[28], const float (&s)[14], const float (&t)[14],
+                                                std::integer_sequence<int, I...> seq) {
+    ((v[2 * I] = conference_row<I>(s, seq) + t[I], v[2 * I + 1] = conference_row<I>(t, seq) - s[I]), ...);
+}
+// v <- H_28 v by its structure: with s = even + odd and t = even - odd
+// entries, the outputs are C s + t and C t - s, 420 additions against 784 of
+// the plain product.  (The signs must be template constants: a constexpr
+// function called in an unrolled loop was evaluated at run time, with the
+// values in dynamically indexed registers; 8192 x 7168 took 806 us, now 131.)
+__device__ __forceinline__ void hadamard28(float (&v)[28]) {
+    float s[14], t[14];
+#pragma unroll
+    for (int j = 0; j < 14; ++j) {
+        s[j] = v[2 * j] + v[2 * j + 1];
+        t[j] = v[2 * j] - v[2 * j + 1];
+    }
+    hadamard28_rows(v, s, t, std::make_integer_sequence<int, 14>{});
 }
 
-// One workgroup per token, k threads; thread j holds channel j of every
+// Two-kernel path: the ring kernel leaves z in memory, then one workgroup per
+// token, k threads; thread j holds channel j of every
 // block (M values), mixes them, and the workgroup reduces the row maximum.
 template <int M>
 __global__ __launch_bounds__(256) void tq_mix_quant_kernel(const float* __restrict__ z, int64_t n,
@@ -2047,17 +2076,10 @@ __global__ __launch_bounds__(256) void tq_mix_quant_kernel(const float* __restri
         for (int b2 = 0; b2 < M2; ++b2) {
             float o[28];
 #pragma unroll
-            for (int a1 = 0; a1 < 28; ++a1) {
-                float acc = 0.0f;
+            for (int b1 = 0; b1 < 28; ++b1) o[b1] = v[b1 * M2 + b2];
+            hadamard28(o);
 #pragma unroll
-                for (int b1 = 0; b1 < 28; ++b1) {
-                    const int sgn = paley28(a1, b1);
-                    acc = sgn > 0 ? acc + v[b1 * M2 + b2] : acc - v[b1 * M2 + b2];
-                }
-                o[a1] = acc;
-            }
-#pragma unroll
-            for (int a1 = 0; a1 < 28; ++a1) v[a1 * M2 + b2] = o[a1];
+            for (int b1 = 0; b1 < 28; ++b1) v[b1 * M2 + b2] = o[b1];
         }
     }
     const float norm = 1.0f / __builtin_sqrtf(static_cast<float>(M));
@@ -2087,6 +2109,250 @@ __global__ __launch_bounds__(256) void tq_mix_quant_kernel(const float* __restri
     }
 }
 
+// Fused variant for rows whose z fits a CU's registers (K rows of M blocks,
+// at most 32 accumulator sets of 16 x 16 per wave: d <= 4096).  One workgroup
+// of 8 waves holds z of 16 TG tokens across the whole row: wave w owns rows 16
+// RG w .. of every block (RG = K / 128), so that the cross-block Hadamard is
+// register arithmetic inside a lane; z never goes to memory (the two-kernel
+// path writes and reads 4 bytes per element) and one launch does it all.
+//
+// T streams through LDS once per workgroup, 32 KiB a step (a block, or a
+// quarter of one at K = 256), with the step's X beside it, in a ring of S
+// stages filled by global_load_lds_dwordx4 S - 1 steps ahead; one barrier per
+// step.  The T stream from L2 (d K 2 bytes per 16 TG tokens) bounds it, so two
+// token groups share it where the registers and the number of workgroups
+// allow.  Units of a row are XOR-swizzled so that 16 rows at one unit, and 8
+// rows at units u and u ^ 2, fall on distinct 16-byte bank groups.
+// Measured against the two kernels: 8192 x 4096, k = 128 63 -> 43 us (two
+// rounds of 16-token workgroups, 36 KiB from L2 per step and CU at about 36
+// bytes per clock), 8192 x 2048 35 -> 16.5 us, 8192 x 4096, k = 256 65 -> 58.
+constexpr int kFhWaves = 8;
+constexpr int kFhThreads = kFhWaves * kWave;
+
+template <int M, int K, int TG>
+struct FhShape {
+    static constexpr int RG = K / 128;             // 16-row groups per wave
+    static constexpr int KC = 16384 / K;           // elements of the reduction per step
+    static constexpr int U = KC / 8;               // 16-byte units per row and step
+    static constexpr int SPB = K / KC;             // steps per block
+    static constexpr int XI = TG * U / 4;          // 1 KiB copies of X per step
+    static constexpr int STAGE = 2048 + XI * 64;   // units per stage
+    static constexpr int S = STAGE * 4 <= 9216 ? 4 : 3;
+    static constexpr bool kFits = RG * TG * M <= 32;
+};
+
+template <int U>
+__device__ __forceinline__ int fh_swz(int r) {
+    return U == 16 ? (r & 1) | ((r >> 3) & 1) << 1 | ((r >> 1) & 3) << 2
+                   : ((r >> 1) & 1) | ((r >> 3) & 1) << 1 | ((r >> 2) & 1) << 2;
+}
+
+template <int M, int K, int TG>
+__global__ __launch_bounds__(kFhThreads) void tq_full_kernel(const uint16_t* __restrict__ X,
+                                                             const uint16_t* __restrict__ T,
+                                                             int64_t n, uint8_t* __restrict__ codes,
+                                                             float* __restrict__ s_x) {
+    using C = FhShape<M, K, TG>;
+    constexpr int RG = C::RG, U = C::U, S = C::S;
+    constexpr int64_t d = int64_t{M} * K;
+    constexpr int TT = 16 * TG;                    // tokens per workgroup
+    constexpr int STEPS = M * C::SPB;
+    constexpr bool P28 = (M % 28) == 0;
+    constexpr int M2 = P28 ? M / 28 : M;           // Sylvester factor
+    static_assert(C::kFits, "z must fit the registers");
+    static_assert(C::XI <= kFhWaves, "at most one X copy per wave and step");
+    // the codes of the tile, one padded row per token, reuse the ring
+    constexpr int CBS = static_cast<int>(d / 2) + 16;
+    static_assert(TT * CBS <= S * C::STAGE * 16, "codes fit the ring");
+    __shared__ __attribute__((aligned(16))) u32x4 ring[S][C::STAGE];
+    __shared__ uint32_t red[kFhWaves][TT];
+
+    const int lane = threadIdx.x & (kWave - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const int l16 = lane & 15, q4 = lane >> 4;
+    const int64_t t0 = static_cast<int64_t>(blockIdx.x) * TT;
+
+    // copies: 4 of T per wave and step, and one of X from the first XI waves;
+    // slot s of a stage's T (or X) holds row s / U, unit (s % U) ^ swz(row)
+    uint32_t toff[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const int sl = (4 * wave + q) * kWave + lane;
+        const int r = sl / U, u = (sl % U) ^ fh_swz<U>(r & 15);
+        toff[q] = static_cast<uint32_t>(r * K * 2 + u * 16);
+    }
+    uint32_t xoff;
+    {
+        const int sl = (wave < C::XI ? wave : 0) * kWave + lane;
+        int r = sl / U;
+        const int u = (sl % U) ^ fh_swz<U>(r & 15);
+        const int64_t last = n - 1 - t0;           // rows past the end: never stored
+        if (r > last) r = static_cast<int>(last);
+        xoff = static_cast<uint32_t>(r * d * 2 + u * 16);
+    }
+    const uint32_t base = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(lds_addr(&ring[0][0])));
+    auto issue = [&](int step) {
+        const int b = step / C::SPB, kc = step % C::SPB;
+        const uint32_t st = base + static_cast<uint32_t>((step % S) * C::STAGE * 16);
+        const uint16_t* tb = T + static_cast<int64_t>(b) * K * K + kc * C::KC;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) dma16(tb, toff[q], st + static_cast<uint32_t>((4 * wave + q) * 1024));
+        if (wave < C::XI)
+            dma16(X + t0 * d + b * K + kc * C::KC, xoff, st + static_cast<uint32_t>(32768 + wave * 1024));
+    };
+
+    f32x4 z[M][RG][TG];
+#pragma unroll
+    for (int p = 0; p < S - 1 && p < STEPS; ++p) issue(p);
+#pragma unroll
+    for (int step = 0; step < STEPS; ++step) {
+        // this wave's copies of the step have landed once at most those of
+        // the later steps are in flight
+        if (step + S - 2 < STEPS) {
+            if (wave < C::XI) wait_vmcnt<(S - 2) * 5>();
+            else wait_vmcnt<(S - 2) * 4>();
+        } else {
+            wait_vmcnt<0>();
+        }
+        lds_barrier();
+        // the stage of step + S - 1 last held step - 1, read before the barrier
+        if (step + S - 1 < STEPS) issue(step + S - 1);
+        const int b = step / C::SPB;
+        const u32x4* ts = &ring[step % S][0];
+        const u32x4* xs = &ring[step % S][2048];
+        if (step % C::SPB == 0) {
+#pragma unroll
+            for (int g = 0; g < RG; ++g)
+#pragma unroll
+                for (int e = 0; e < TG; ++e) z[b][g][e] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+        }
+#pragma unroll
+        for (int s = 0; s < C::KC / 32; ++s) {
+            const int pos = (4 * s + q4) ^ fh_swz<U>(l16);
+            u32x4 xf[TG];
+#pragma unroll
+            for (int e = 0; e < TG; ++e) xf[e] = xs[(16 * e + l16) * U + pos];
+#pragma unroll
+            for (int g = 0; g < RG; ++g) {
+                const u32x4 tf = ts[(16 * (RG * wave + g) + l16) * U + pos];
+#pragma unroll
+                for (int e = 0; e < TG; ++e)
+                    z[b][g][e] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(tf), as_bf16x8(xf[e]),
+                                                                        z[b][g][e], 0, 0, 0);
+            }
+        }
+    }
+
+    // lane (token 16 e + l16, q4) holds channels 16 (RG wave + g) + 4 q4 + r
+    // of every block; the Hadamard over b, then the row maximum
+    const float norm = 1.0f / __builtin_sqrtf(static_cast<float>(M));
+    uint32_t mx[TG];
+#pragma unroll
+    for (int e = 0; e < TG; ++e) {
+        mx[e] = 0;
+#pragma unroll
+        for (int g = 0; g < RG; ++g)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+#pragma unroll
+                for (int hstep = 1; hstep < M2; hstep <<= 1)
+#pragma unroll
+                    for (int b = 0; b < M; ++b)
+                        if (((b % M2) & hstep) == 0) {
+                            const float x = z[b][g][e][r], y = z[b + hstep][g][e][r];
+                            z[b][g][e][r] = x + y;
+                            z[b + hstep][g][e][r] = x - y;
+                        }
+                if constexpr (P28) {
+#pragma unroll
+                    for (int b2 = 0; b2 < M2; ++b2) {
+                        float o[28];
+#pragma unroll
+                        for (int b1 = 0; b1 < 28; ++b1) o[b1] = z[b1 * M2 + b2][g][e][r];
+                        hadamard28(o);
+#pragma unroll
+                        for (int b1 = 0; b1 < 28; ++b1) z[b1 * M2 + b2][g][e][r] = o[b1];
+                    }
+                }
+#pragma unroll
+                for (int b = 0; b < M; ++b) {
+                    z[b][g][e][r] *= norm;
+                    mx[e] = max(mx[e], abs_bits(z[b][g][e][r]));
+                }
+            }
+#pragma unroll
+        for (int x = 16; x < kWave; x <<= 1)
+            mx[e] = max(mx[e], static_cast<uint32_t>(__shfl_xor(static_cast<int>(mx[e]), x)));
+        if (q4 == 0) red[wave][16 * e + l16] = mx[e];
+    }
+    lds_barrier();                                 // and every wave is past the ring
+    uint8_t* const cbuf = reinterpret_cast<uint8_t*>(&ring[0][0]);
+#pragma unroll
+    for (int e = 0; e < TG; ++e) {
+        const int tok = 16 * e + l16;
+#pragma unroll
+        for (int w = 0; w < kFhWaves; ++w) mx[e] = max(mx[e], red[w][tok]);
+        const float amax = __uint_as_float(mx[e]);
+        if (wave == 0 && q4 == 0 && t0 + tok < n) s_x[t0 + tok] = __fdiv_rn(amax, kQmax4);
+        const bool nz = amax > 0.0f;
+        const float inv = nz ? __fdiv_rn(kQmax4, amax) : 0.0f;
+#pragma unroll
+        for (int b = 0; b < M; ++b)
+#pragma unroll
+            for (int g = 0; g < RG; ++g) {
+                uint32_t p = 0;
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    p |= (fq_round1<7, false>(z[b][g][e][r], inv, 0.0f) & 0xFu) << (4 * r);
+                const int c = b * K + 16 * (RG * wave + g) + 4 * q4;
+                *reinterpret_cast<uint16_t*>(cbuf + tok * CBS + c / 2) = static_cast<uint16_t>(nz ? p : 0u);
+            }
+    }
+    lds_barrier();
+    constexpr int PER = static_cast<int>(d / 32);  // 16-byte pieces per token
+    for (int i = threadIdx.x; i < TT * PER; i += kFhThreads) {
+        const int tok = i / PER, pc = i % PER;
+        if (t0 + tok < n)
+            *reinterpret_cast<u32x4*>(codes + (t0 + tok) * (d / 2) + 16 * pc) =
+                *reinterpret_cast<const u32x4*>(cbuf + tok * CBS + 16 * pc);
+    }
+}
+
+// A step takes about 0.45 us (36 KiB from L2 into LDS) however few tokens
+// there are, the two kernels 9 us and a microsecond per 5.5 MB moved (10.5
+// bytes an element): 300 x 4096, k = 128 took 16.5 us fused and 13.4 us as two
+// kernels, 8192 x 4096 43 and 64 us.
+template <int M, int K>
+static bool tq_full_fused_pays(int64_t n, int64_t cus) {
+    const bool two = FhShape<M, K, 2>::kFits && (n + 31) / 32 >= cus;
+    const int64_t groups = two ? (n + 31) / 32 : (n + 15) / 16;
+    const double fused = static_cast<double>((groups + cus - 1) / cus) * M * FhShape<M, K, 1>::SPB *
+                         (two ? 0.5 : 0.45);
+    return fused < 9.0 + static_cast<double>(n) * M * K * (10.5 / 5.5e6);
+}
+
+// Launches the fused kernel where z of a row fits (see FhShape); false: the
+// two-kernel path.  Two token groups per workgroup where they fit and still
+// give every CU a workgroup.
+template <int M, int K>
+static bool launch_tq_full(const uint16_t* X, int64_t n, const uint16_t* T, uint8_t* codes, float* s_x,
+                           int64_t cus, hipStream_t stream) {
+    if (!tq_full_fused_pays<M, K>(n, cus)) return false;
+    if constexpr (FhShape<M, K, 2>::kFits) {
+        if ((n + 31) / 32 >= cus) {
+            hipLaunchKernelGGL((tq_full_kernel<M, K, 2>), dim3(static_cast<uint32_t>((n + 31) / 32)),
+                               dim3(kFhThreads), 0, stream, X, T, n, codes, s_x);
+            return true;
+        }
+    }
+    if constexpr (FhShape<M, K, 1>::kFits) {
+        hipLaunchKernelGGL((tq_full_kernel<M, K, 1>), dim3(static_cast<uint32_t>((n + 15) / 16)),
+                           dim3(kFhThreads), 0, stream, X, T, n, codes, s_x);
+        return true;
+    }
+    return false;
+}
+
 static bool tq_full_supported_m(int64_t m) {
     switch (m) {
         case 2: case 4: case 8: case 16: case 32: case 64: case 28: case 56: case 112: return true;
@@ -2113,6 +2379,18 @@ hipError_t launch_transform_quant_full(const void* X, int64_t n, int64_t d, cons
     if (err != hipSuccess) return err;
     err = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
     if (err != hipSuccess) return err;
+    bool fused = false;
+    switch (d / k) {
+#define CAT_FULL(MM)                                                                       \
+    case MM:                                                                               \
+        fused = k == 128 ? launch_tq_full<MM, 128>(Xb, n, Tb, codes, s_x, cus, stream)     \
+                         : launch_tq_full<MM, 256>(Xb, n, Tb, codes, s_x, cus, stream);    \
+        break;
+        CAT_FULL(2) CAT_FULL(4) CAT_FULL(8) CAT_FULL(16) CAT_FULL(28) CAT_FULL(32)
+#undef CAT_FULL
+        default: break;
+    }
+    if (fused) return hipGetLastError();
     auto zpass = [&](auto kc) -> hipError_t {
         constexpr int K = decltype(kc)::value;
         int64_t R = 0;
