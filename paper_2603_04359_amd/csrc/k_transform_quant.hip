@@ -28,8 +28,9 @@
 //   whole rows      (fp32 operands and other bf16 blocks of at least 16,
 //                   d <= 4096; tq_rows_kernel) one launch, a workgroup holds
 //                   the whole rows of 16 tokens.
-// Two-pass kernels, by case: tq_group_kernel (bf16, k <= 256, d a multiple
-// of 256), tq_ring_kernel (bf16 k = 512, and k = 128 or 256 otherwise),
+// Two-pass kernels, by case: tq_wide_kernel (bf16, k = 128, 256, 512, d a
+// multiple of 256), tq_group_kernel (bf16, k = 32, 64, d a multiple of 256),
+// tq_ring_kernel (bf16 k = 128 otherwise, and k = 512 for few tokens),
 // tq_mfma_kernel (bf16 k = 32, 64 otherwise) and the vector-ALU kernels (the
 // rest).  The asymmetric INT4 variant takes the same routes with a row maximum
 // and minimum, except that bf16 k = 32 and 64 off the group kernel's widths go
@@ -1410,7 +1411,7 @@ __global__ __launch_bounds__(kFqThreads, 1) void tq_fused_kernel(
 }
 
 // ------------------------------------------------ group two-pass path
-// bf16, k in {32, 64, 128, 256} with d a multiple of 256.  One persistent
+// bf16, k = 32 or 64 with d a multiple of 256.  One persistent
 // workgroup per CU owns a group of 256 channels (one or more whole blocks)
 // for the token tiles r, r + R, ...  Six waves with fixed roles:
 //   waves 0-3  compute: wave w holds rows 64 w .. + 63 of the group's T
@@ -1427,8 +1428,8 @@ __global__ __launch_bounds__(kFqThreads, 1) void tq_fused_kernel(
 // Pass 1 folds per-token maxima of the four waves with LDS atomics; the
 // tile's maxima go to the global per-token words one step later (after the
 // next barrier), which needs no barrier of its own.
-// (At k = 512 the 64 rows x 512 columns of T a wave would hold do not fit
-// its registers; that case runs on the ring kernels.)
+// (Larger blocks run on the wide kernel below, which measured 3-20% faster
+// there and the same at k = 32 and 64.)
 constexpr int kTgCompute = 4;
 constexpr int kTgCopy = 2;
 constexpr int kTgThreads = (kTgCompute + kTgCopy) * kWave;
@@ -1458,7 +1459,7 @@ __global__ __launch_bounds__(kTgThreads, 1) void tq_group_kernel(
     const uint16_t* __restrict__ X, const uint16_t* __restrict__ T, int64_t n, int64_t d,
     int64_t R, uint32_t* __restrict__ ws, uint8_t* __restrict__ codes, float* __restrict__ s_x,
     float* __restrict__ zmin_x) {
-    static_assert(K == 32 || K == 64 || K == 128 || K == 256, "block size");
+    static_assert(K == 32 || K == 64, "block size");
     constexpr int NS = K / 16;                          // 16-deep MFMA steps
     constexpr int NSB = kTgTT / 32;                     // 32-token subtiles
     constexpr bool kShare = K >= 64;                    // both row groups in one block
@@ -1675,11 +1676,370 @@ hipError_t launch_tq_group(const uint16_t* X, int64_t n, int64_t d, const uint16
     return hipGetLastError();
 }
 
-// The group kernels take bf16 k in {32, 64, 128, 256} when d is a multiple
-// of 256.
-static bool tq_group_fits(int64_t d, int64_t k) {
-    return (k == 32 || k == 64 || k == 128 || k == 256) && d % 256 == 0;
+// ------------------------------------------------- wide two-pass path
+// bf16, k = 128, 256 or 512, d a multiple of 256 and of k.  One persistent
+// workgroup of 8 waves per CU owns 256 output rows (two blocks, one, or half
+// of one) for the token tiles r, r + R, ...  (a tile is 64 tokens).  Wave w
+// holds rows 32 w .. + 31 of T in registers (32 to 128 of them) and multiplies
+// them with all 64 tokens, read from a 2-stage LDS ring.
+//
+// At k = 128 and 256 it is bound by the X stream (3.8-4.1 TB/s in pass 1), at
+// k = 512 by how well a SIMD's MFMAs stay fed, so nothing else gets a phase of
+// its own: while tile i is multiplied, the copies of tile i + 1 are issued
+// between the first MFMAs and, up to k = 256, tile i - 1's accumulators (kept
+// in a second set) are folded or rounded between all of them, a few values per
+// step.  Two waves per SIMD cover each other's copy issue.  A tile's codes
+// leave as 8 bytes per lane, 128 contiguous bytes per token over the 8 waves.
+// Against the kernels that ran these cases before (group kernel up to 256, ring
+// kernel at 512), whole calls, INT4:
+//   16384 x 8192, k = 512   328 -> 241 us (passes 108 and 121 us at best)
+//   4096 x 4096, k = 512     55 -> 38 us (8-bit)
+//   8192 x 14336, k = 256   144 -> 134 us; 300 x 4096 15.8 -> 11.7 us
+//   8192 x 14336, k = 128   112 -> 102 us
+constexpr int kTwWaves = 8;
+constexpr int kTwThreads = kTwWaves * kWave;
+constexpr int kTwTT = 64;                   // tokens per tile
+constexpr int kTwRows = 256;                // output rows per workgroup
+// channels of X that a workgroup's rows read: 256 / k blocks, or one of 512
+constexpr int tw_span(int k) { return k < 256 ? 256 : k; }
+
+template <int K, bool QUANT, int QM, bool ASYM>
+__global__ __launch_bounds__(kTwThreads, 1) void tq_wide_kernel(
+    const uint16_t* __restrict__ X, const uint16_t* __restrict__ T, int64_t n, int64_t d,
+    int64_t R, uint32_t* __restrict__ ws, uint8_t* __restrict__ codes, float* __restrict__ s_x,
+    float* __restrict__ zmin_x) {
+    static_assert(K == 128 || K == 256 || K == 512, "block size");
+    static_assert(!ASYM || QM == 7, "asymmetric codes are INT4");
+    constexpr int KT = tw_span(K);                  // channels of a token tile
+    constexpr int NS = K / 16;                      // 16-deep MFMA steps
+    constexpr int U = KT / 8;                       // 16-byte units per token row
+    constexpr int STAGE = kTwTT * U;                // units per stage (32 or 64 KiB)
+    constexpr int OPS = STAGE / (kTwWaves * kWave); // copies per wave and tile
+    constexpr int VPS = 32 / NS;                    // old values handled per step
+    constexpr int HALVES = KT / kTwRows;            // workgroups per span
+    // A second accumulator set, so that a tile's values are handled beside the
+    // next tile's MFMAs, where the registers have room for it (at k = 512 it
+    // spilled: 256 + 301 us for the two passes at 16384 x 8192)
+    constexpr bool OVERLAP = K <= 256;
+    constexpr int kLag = OVERLAP ? 2 : 1;           // tiles from a barrier back to finished maxima
+    // X fragments are read PD steps ahead of their MFMAs: two waves per SIMD
+    // alone do not cover the LDS latency (a step took 270 clocks for 128 of
+    // MFMAs)
+    constexpr int PD = OVERLAP ? 2 : 3;
+    __shared__ __attribute__((aligned(16))) u32x4 ring[2][STAGE];
+    __shared__ uint32_t words[QUANT ? 4 : 1][QUANT ? (ASYM ? 2 : 1) : 1][kTwTT];
+    __shared__ uint32_t red[QUANT ? 1 : 2][ASYM ? 2 : 1][QUANT ? 1 : kTwTT];
+
+    // workgroup -> (span, tile row) unit and half; the halves of a unit are 8
+    // apart in launch order, so that they run on one XCD and share X in its L2
+    const int64_t nb = d / KT;
+    int64_t unit = blockIdx.x;
+    int half = 0;
+    if constexpr (HALVES > 1) {
+        const int64_t sq = blockIdx.x >> 3;
+        half = static_cast<int>(sq % HALVES);
+        unit = (sq / HALVES) * 8 + (blockIdx.x & 7);
+    }
+    const int64_t ntiles = (n + kTwTT - 1) / kTwTT;
+    if (unit >= nb * R) return;
+    const int64_t b = unit % nb, r0 = unit / nb;
+    if (r0 >= ntiles) return;
+    const int64_t nt = (ntiles - r0 + R - 1) / R;   // tiles of this workgroup
+    const int lane = threadIdx.x & (kWave - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const int l32 = lane & 31, h = lane >> 5;
+    auto tile0 = [&](int64_t it) { return (r0 + it * R) * kTwTT; };
+    const int64_t ch = b * KT + half * kTwRows + wave * 32;   // this wave's first channel
+    const int xo = (wave * 32 % KT) / K * (K / 8);  // first unit of its block in a tile row
+
+    // Copy q of this wave fills slots (wave OPS + q) 64 ..; slot s of a stage
+    // holds token row s / U, unit (s % U) ^ swz(row).  swz touches the low four
+    // bits, so that the fragments of eight steps share an address register and
+    // differ in immediates; 16 rows at one unit, and 8 rows at units u and u ^
+    // 1, fall on distinct 16-byte bank groups.
+    auto swz = [](int r) { return ((r & 7) << 1) | ((r >> 3) & 1); };
+    const uint32_t lds0 = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(lds_addr(&ring[0][wave * OPS * kWave])));
+    auto copy = [&](int64_t it, int st, int q) {
+        const int64_t t0 = tile0(it);
+        const int last = static_cast<int>(n - 1 - t0 < kTwTT ? n - 1 - t0 : kTwTT);   // rows past the end: never used
+        const uint32_t dst = lds0 + static_cast<uint32_t>(st * STAGE * 16 + q * 1024);
+        if constexpr (U == kWave) {
+            // one row per copy: a wave-uniform address
+            const int r = wave * OPS + q;
+            dma16(X + (t0 + (r < last ? r : last)) * d + b * KT, static_cast<uint32_t>((lane ^ swz(r & 15)) * 16), dst);
+        } else {
+            const int sl = (wave * OPS + q) * kWave + lane;
+            const int r = sl / U;
+            dma16(X + t0 * d + b * KT, static_cast<uint32_t>(((r < last ? r : last) * d + ((sl % U) ^ swz(r & 15)) * 8) * 2),
+                  dst);
+        }
+    };
+    // pass 2: the tile's finished row words (wave 0 the maxima, wave 1 the
+    // minima of asymmetric codes)
+    auto copy_words = [&](int64_t it) {
+        if constexpr (QUANT) {
+            if (wave < (ASYM ? 2 : 1)) {
+                const int64_t t0 = tile0(it);
+                const int64_t last = n - 1 - t0;
+                const int j = lane <= last ? lane : static_cast<int>(last);
+                dma4(ws + (wave ? n : 0) + t0, static_cast<uint32_t>(j * 4),
+                     lds_addr(&words[it & 3][ASYM ? wave : 0][0]));
+            }
+        }
+    };
+    // A operand: row fq_row(l32) of this wave's 32, so that a lane ends up
+    // with 16 consecutive channels (16 h ..) of one token.  It comes through
+    // the ring, each wave through an eighth of its own and from k = 256 on in
+    // two halves of the columns: read straight into fragments, with
+    // consecutive lanes on different rows, the 256 KiB of a workgroup took 8
+    // us at k = 512.
+    u32x4 tf[NS];
+    {
+        constexpr int PARTS = K >= 256 ? 2 : 1;
+        constexpr int PU = K / 8 / PARTS;           // units per row and part
+        const u32x4* tl = &ring[0][0] + wave * (32 * PU);
+        const uint32_t dst = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(lds_addr(tl)));
+#pragma unroll
+        for (int pt = 0; pt < PARTS; ++pt) {
+#pragma unroll
+            for (int q = 0; q < PU / 2; ++q) {
+                const int sl = q * kWave + lane, r = sl / PU;
+                const int u = (sl % PU) ^ swz(r & 15);
+                dma16(T + ch * K + pt * (K / PARTS), static_cast<uint32_t>(fq_row(r) * K * 2 + u * 16),
+                      dst + static_cast<uint32_t>(q * 1024));
+            }
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+#pragma unroll
+            for (int s = 0; s < NS / PARTS; ++s)
+                tf[pt * (NS / PARTS) + s] = tl[l32 * PU + (((2 * s + h) & 15) ^ swz(l32 & 15)) + ((2 * s) & ~15)];
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        }
+    }
+    lds_barrier();
+#pragma unroll
+    for (int q = 0; q < OPS; ++q) copy(0, 0, q);
+    copy_words(0);
+    if constexpr (!QUANT) {
+        for (int i = threadIdx.x; i < 2 * (ASYM ? 2 : 1) * kTwTT; i += kTwThreads) (&red[0][0][0])[i] = 0u;
+    }
+    // pass 1: fold a finished tile's LDS maxima into the global words
+    auto flush = [&](int64_t it) {
+        const int p = static_cast<int>(it & 1);
+        const int64_t t = tile0(it) + lane;
+        const uint32_t m = red[p][0][lane];
+        red[p][0][lane] = 0u;
+        if constexpr (ASYM) {
+            const uint32_t mn = red[p][1][lane];
+            red[p][1][lane] = 0u;
+            if (t < n) {
+                atomicMax(ws + t, m);
+                atomicMax(ws + n + t, mn);
+            }
+        } else {
+            if (t < n && m) atomicMax(ws + t, m);
+        }
+    };
+
+    // the previous tile's work, in VPS values per step: token group e = 0, 1
+    // (32 tokens), values 0 .. 15 of each
+    struct Old {
+        uint32_t mx[2], mn[2];       // pass 1: running folds (signed / unsigned, or keys)
+        float inv[2], zmin[2];       // pass 2
+        uint32_t c[QM == 7 ? 2 : 4]; // codes of one token group, filled from the low end
+    };
+    auto old_begin = [&](int64_t it, Old& o) {
+        if constexpr (!QUANT) {
+            o.mx[0] = o.mx[1] = ASYM ? 0u : 0x80000000u;    // signed minimum
+            o.mn[0] = o.mn[1] = 0u;
+        } else {
+#pragma unroll
+            for (int e = 0; e < 2; ++e) {
+                const int j = 32 * e + l32;
+                const int64_t t = tile0(it) + j;
+                float s;
+                if constexpr (ASYM) {
+                    asym_scale(words[it & 3][0][j], words[it & 3][1][j], o.zmin[e], s, o.inv[e]);
+                } else {
+                    const float amax = __uint_as_float(words[it & 3][0][j]);
+                    s = __fdiv_rn(amax, static_cast<float>(QM));
+                    o.inv[e] = amax > 0.0f ? __fdiv_rn(static_cast<float>(QM), amax) : 0.0f;
+                    o.zmin[e] = 0.0f;
+                }
+                if (wave == 0 && half == 0 && b == 0 && h == 0 && t < n) {
+                    s_x[t] = s;
+                    if constexpr (ASYM) zmin_x[t] = o.zmin[e];
+                }
+            }
+        }
+    };
+    auto old_piece = [&](int64_t it, int v, const f32x16 (&z)[2], Old& o) {
+        const int e = v >> 4, i = v & 15;
+        if constexpr (!QUANT) {
+            if constexpr (ASYM) {
+                const uint32_t key = fkey(z[e][i]);
+                o.mx[e] = max(o.mx[e], key);
+                o.mn[e] = max(o.mn[e], ~key);
+            } else {
+                // see fq_absmax16: the largest as signed and as unsigned bits
+                const uint32_t u = __float_as_uint(z[e][i]);
+                o.mx[e] = static_cast<uint32_t>(max(static_cast<int32_t>(o.mx[e]), static_cast<int32_t>(u)));
+                o.mn[e] = max(o.mn[e], u);
+            }
+        } else {
+            // the code's bits enter at the top of its word, which shifts down
+            const uint32_t w = fq_round1<QM, ASYM>(z[e][i], o.inv[e], o.zmin[e]);
+            constexpr int kPer = QM == 7 ? 8 : 4;        // codes per word
+            uint32_t& c = o.c[i / kPer];
+            c = __builtin_amdgcn_alignbit(w, i % kPer ? c : 0u, 32 / kPer);
+            if (i == 15) {
+                const int64_t t = tile0(it) + 32 * e + l32;
+                if (t < n) {
+                    if constexpr (QM == 7)
+                        *reinterpret_cast<u32x2*>(codes + t * (d / 2) + (ch + 16 * h) / 2) = u32x2{o.c[0], o.c[1]};
+                    else
+                        *reinterpret_cast<u32x4*>(codes + t * d + ch + 16 * h) =
+                            u32x4{o.c[0], o.c[1], o.c[2 % (QM == 7 ? 2 : 4)], o.c[3 % (QM == 7 ? 2 : 4)]};
+                }
+            }
+        }
+    };
+    auto old_end = [&](int64_t it, const Old& o) {
+        if constexpr (!QUANT) {
+#pragma unroll
+            for (int e = 0; e < 2; ++e) {
+                uint32_t m = o.mx[e];
+                if constexpr (!ASYM)
+                    m = max(static_cast<uint32_t>(max(static_cast<int32_t>(m), 0)), o.mn[e] & 0x7FFFFFFFu);
+                m = max(m, static_cast<uint32_t>(__shfl_xor(static_cast<int>(m), 32)));
+                if (h == 0) atomicMax(&red[it & 1][0][32 * e + l32], m);
+                if constexpr (ASYM) {
+                    const uint32_t mn = max(o.mn[e], static_cast<uint32_t>(__shfl_xor(static_cast<int>(o.mn[e]), 32)));
+                    if (h == 0) atomicMax(&red[it & 1][1][32 * e + l32], mn);
+                }
+            }
+        }
+    };
+
+    // Step it: tile it multiplied into cur while tile it - 1, kept in old, is
+    // folded or rounded (with_old); without OVERLAP tile it itself is, after
+    // its last MFMA.
+    auto tile_step = [&](int64_t it, f32x16 (&cur)[2], const f32x16 (&old)[2], auto with_old) {
+        constexpr bool OLD = decltype(with_old)::value;
+        const int st = static_cast<int>(it & 1);
+        wait_vmcnt<0>();            // this wave's copies of the tile
+        lds_barrier();              // everyone's; the other stage is free
+        if constexpr (!QUANT) {
+            if (wave == 0 && it >= kLag) flush(it - kLag);
+        }
+        Old o;
+        if constexpr (OLD) old_begin(it - 1, o);
+        // past the last tile the copies repeat it (never read)
+        const int64_t nx = it + 1 < nt ? it + 1 : it;
+        cur[0] = f32x16{};
+        cur[1] = f32x16{};
+        u32x4 xf[PD + 1][2];
+        auto read = [&](int s) {
+            const int pos = l32 * U + xo + (((2 * s + h) & 15) ^ swz(l32 & 15)) + ((2 * s) & ~15);
+            xf[s % (PD + 1)][0] = ring[st][pos];
+            xf[s % (PD + 1)][1] = ring[st][32 * U + pos];
+        };
+#pragma unroll
+        for (int s = 0; s < PD; ++s) read(s);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int s = 0; s < NS; ++s) {
+            if (s + PD < NS) read(s + PD);
+            cur[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(tf[s]), as_bf16x8(xf[s % (PD + 1)][0]), cur[0], 0, 0, 0);
+            cur[1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(tf[s]), as_bf16x8(xf[s % (PD + 1)][1]), cur[1], 0, 0, 0);
+#pragma unroll
+            for (int q = 0; q < OPS; ++q)          // in the first half of the steps
+                if (q * NS / (2 * OPS) == s) copy(nx, st ^ 1, q);
+            if constexpr (OLD) {
+#pragma unroll
+                for (int v = 0; v < VPS; ++v) old_piece(it - 1, VPS * s + v, old, o);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        copy_words(nx);
+        if constexpr (OLD) old_end(it - 1, o);
+    };
+    auto whole_tile = [&](int64_t it, const f32x16 (&z)[2]) {
+        Old o;
+        old_begin(it, o);
+#pragma unroll
+        for (int v = 0; v < 32; ++v) old_piece(it, v, z, o);
+        old_end(it, o);
+    };
+    f32x16 za[2];
+    int64_t it = 1;
+    if constexpr (OVERLAP) {
+        f32x16 zb[2];
+        tile_step(0, za, zb, std::false_type{});
+        for (; it + 1 < nt; it += 2) {
+            tile_step(it, zb, za, std::true_type{});
+            tile_step(it + 1, za, zb, std::true_type{});
+        }
+        const bool in_b = it < nt;      // one more tile, into zb
+        if (in_b) {
+            tile_step(it, zb, za, std::true_type{});
+            ++it;
+        }
+        // the last tile's accumulators
+        wait_vmcnt<0>();
+        lds_barrier();
+        if constexpr (!QUANT) {
+            if (wave == 0 && it >= kLag) flush(it - kLag);
+        }
+        if (in_b) whole_tile(it - 1, zb);
+        else whole_tile(it - 1, za);
+    } else {
+        for (it = 0; it < nt; ++it) {
+            tile_step(it, za, za, std::false_type{});
+            whole_tile(it, za);
+        }
+    }
+    wait_vmcnt<0>();
+    if constexpr (!QUANT) {
+        lds_barrier();
+        if (wave == 0) flush(it - 1);
+    }
 }
+
+template <int K, int QM, bool ASYM = false>
+hipError_t launch_tq_wide(const uint16_t* X, int64_t n, int64_t d, const uint16_t* T, uint8_t* codes,
+                          float* s_x, uint32_t* ws, hipStream_t stream, float* zmin_x = nullptr) {
+    int dev = 0, cus = 0;
+    hipError_t err = hipGetDevice(&dev);
+    if (err != hipSuccess) return err;
+    err = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+    if (err != hipSuccess) return err;
+    constexpr int64_t halves = tw_span(K) / kTwRows;
+    const int64_t nb = d / tw_span(K), ntiles = (n + kTwTT - 1) / kTwTT;
+    // one workgroup per CU: R token-tile rows, rounded down so that every
+    // workgroup is resident at once
+    int64_t R = cus / halves / nb;
+    if (R > ntiles) R = ntiles;
+    if (R < 1) R = 1;
+    const int64_t units = nb * R;
+    const dim3 grid(static_cast<uint32_t>(halves > 1 ? (units + 7) / 8 * 8 * halves : units)), block(kTwThreads);
+    err = launch_fill_zero(ws, ASYM ? 2 * n : n, stream);
+    if (err != hipSuccess) return err;
+    hipLaunchKernelGGL((tq_wide_kernel<K, false, 7, ASYM>), grid, block, 0, stream, X, T, n, d, R, ws,
+                       codes, s_x, zmin_x);
+    err = hipGetLastError();
+    if (err != hipSuccess) return err;
+    hipLaunchKernelGGL((tq_wide_kernel<K, true, QM, ASYM>), grid, block, 0, stream, X, T, n, d, R, ws,
+                       codes, s_x, zmin_x);
+    return hipGetLastError();
+}
+
+// The group (k = 32, 64) and wide (k = 128, 256, 512) kernels take whole spans.
+static bool tq_spans_fit(int64_t d, int64_t k) { return k >= 32 && d % tw_span(static_cast<int>(k)) == 0; }
+// At k = 512 a call of few tiles is all ramp, and the ring kernel's workgroups
+// load half as much of T: 64 x 1024 took 14.4 us there and 15.5 us on the wide
+// kernel, 256 x 4096 15.5 and 16.5; 128 x 14336 24.6 and 18.3, 700 x 2560
+// (asymmetric) 22.6 and 16.5.
+static bool tq_ring_512(int64_t n, int64_t d) { return n * d <= int64_t{1} << 20; }
 
 // Grid of the ring kernels: two resident workgroups per CU, R token-tile
 // rows per block rounded down so that every workgroup is resident at once
@@ -1877,14 +2237,17 @@ static hipError_t launch_tq_qm(const void* X, int x_bf16, int64_t n, int64_t d, 
     }
     amax_ws = reinterpret_cast<uint32_t*>(reinterpret_cast<uint8_t*>(amax_ws) +
                                           tq_twopass_offset(n, d));
-    if (x_bf16 && t_bf16 && tq_group_fits(d, k)) {
+    if (x_bf16 && t_bf16 && tq_spans_fit(d, k)) {
         const uint16_t* Xb = static_cast<const uint16_t*>(X);
         const uint16_t* Tb = static_cast<const uint16_t*>(T);
         switch (k) {
             case 32: return launch_tq_group<32, QM>(Xb, n, d, Tb, codes, s_x, amax_ws, stream);
             case 64: return launch_tq_group<64, QM>(Xb, n, d, Tb, codes, s_x, amax_ws, stream);
-            case 128: return launch_tq_group<128, QM>(Xb, n, d, Tb, codes, s_x, amax_ws, stream);
-            case 256: return launch_tq_group<256, QM>(Xb, n, d, Tb, codes, s_x, amax_ws, stream);
+            case 128: return launch_tq_wide<128, QM>(Xb, n, d, Tb, codes, s_x, amax_ws, stream);
+            case 256: return launch_tq_wide<256, QM>(Xb, n, d, Tb, codes, s_x, amax_ws, stream);
+            case 512:
+                if (tq_ring_512(n, d)) break;
+                return launch_tq_wide<512, QM>(Xb, n, d, Tb, codes, s_x, amax_ws, stream);
             default: break;
         }
     }
@@ -1895,7 +2258,6 @@ static hipError_t launch_tq_qm(const void* X, int x_bf16, int64_t n, int64_t d, 
             case 32: return launch_tq_mfma<32, 32, QM>(Xb, n, d, Tb, codes, s_x, amax_ws, stream);
             case 64: return launch_tq_mfma<64, 64, QM>(Xb, n, d, Tb, codes, s_x, amax_ws, stream);
             case 128: return launch_tq_ring<128, QM>(Xb, n, d, Tb, codes, s_x, amax_ws, stream);
-            case 256: return launch_tq_ring<256, QM>(Xb, n, d, Tb, codes, s_x, amax_ws, stream);
             case 512: return launch_tq_ring<512, QM>(Xb, n, d, Tb, codes, s_x, amax_ws, stream);
             default: break;
         }
@@ -1947,9 +2309,8 @@ static hipError_t launch_tq_generic_asym(const XT* X, int64_t n, int64_t d, cons
 
 // Asymmetric INT4: the single-pass kernel for bf16 with k = 128 and d =
 // 2048, 4096 or 8192 (row max and min keys exchanged as two words); else two
-// passes (row max and min keys, then codes): the group kernels for bf16
-// with k <= 256 and d a multiple of 256, the ring kernels for bf16 with k in
-// {128, 256, 512} otherwise, else the vector ALU.
+// passes (row max and min keys, then codes) on the symmetric codes' kernels,
+// or whole rows.
 hipError_t launch_transform_quant_asym(const void* X, int x_bf16, int64_t n, int64_t d,
                                        const void* T, int t_bf16, int64_t k, uint8_t* codes,
                                        float* s_x, float* zmin_x, uint32_t* ws,
@@ -1962,14 +2323,17 @@ hipError_t launch_transform_quant_asym(const void* X, int x_bf16, int64_t n, int
         if (e != hipSuccess || launched) return e;
     }
     ws = reinterpret_cast<uint32_t*>(reinterpret_cast<uint8_t*>(ws) + tq_twopass_offset(n, d));
-    if (x_bf16 && t_bf16 && tq_group_fits(d, k)) {
+    if (x_bf16 && t_bf16 && tq_spans_fit(d, k)) {
         const uint16_t* Xb = static_cast<const uint16_t*>(X);
         const uint16_t* Tb = static_cast<const uint16_t*>(T);
         switch (k) {
             case 32: return launch_tq_group<32, 7, true>(Xb, n, d, Tb, codes, s_x, ws, stream, zmin_x);
             case 64: return launch_tq_group<64, 7, true>(Xb, n, d, Tb, codes, s_x, ws, stream, zmin_x);
-            case 128: return launch_tq_group<128, 7, true>(Xb, n, d, Tb, codes, s_x, ws, stream, zmin_x);
-            case 256: return launch_tq_group<256, 7, true>(Xb, n, d, Tb, codes, s_x, ws, stream, zmin_x);
+            case 128: return launch_tq_wide<128, 7, true>(Xb, n, d, Tb, codes, s_x, ws, stream, zmin_x);
+            case 256: return launch_tq_wide<256, 7, true>(Xb, n, d, Tb, codes, s_x, ws, stream, zmin_x);
+            case 512:
+                if (tq_ring_512(n, d)) break;
+                return launch_tq_wide<512, 7, true>(Xb, n, d, Tb, codes, s_x, ws, stream, zmin_x);
             default: break;
         }
     }
@@ -1978,7 +2342,6 @@ hipError_t launch_transform_quant_asym(const void* X, int x_bf16, int64_t n, int
         const uint16_t* Tb = static_cast<const uint16_t*>(T);
         switch (k) {
             case 128: return launch_tq_ring<128, 7, true>(Xb, n, d, Tb, codes, s_x, ws, stream, zmin_x);
-            case 256: return launch_tq_ring<256, 7, true>(Xb, n, d, Tb, codes, s_x, ws, stream, zmin_x);
             case 512: return launch_tq_ring<512, 7, true>(Xb, n, d, Tb, codes, s_x, ws, stream, zmin_x);
             default:
                 return launch_tq_generic_asym(Xb, n, d, Tb, k, codes, s_x, zmin_x, ws, stream);
@@ -2401,7 +2764,8 @@ hipError_t launch_transform_quant_full(const void* X, int64_t n, int64_t d, cons
         return hipGetLastError();
     };
     // the z pass stays on the ring kernels: writing fp32 z, two workgroups
-    // per CU (measured 43 us at 8192 x 4096) beat the group kernel (59 us)
+    // per CU (measured 43 us at 8192 x 4096) beat one workgroup per CU with 256-channel
+    // tiles (59 us)
     err = k == 128 ? zpass(std::integral_constant<int, 128>{})
                    : zpass(std::integral_constant<int, 256>{});
     if (err != hipSuccess) return err;
