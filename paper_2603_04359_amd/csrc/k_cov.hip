@@ -386,7 +386,11 @@ __global__ __launch_bounds__(kCovFThreads) void cov_f64_kernel(const XT* __restr
 // A tile covered whole by one workgroup is added into acc directly; the
 // pieces of a split tile go to per-workgroup slots of the workspace with
 // plain stores, and cov_combine_kernel adds them into acc in a fixed order
-// (deterministic, no atomics) and writes every tile's mirror image.
+// (deterministic, no atomics) and writes every tile's mirror image.  A split
+// diagonal tile keeps only its 64 x 64 blocks on and above the diagonal, 10 of
+// 16: a block-diagonal batch is mostly such pieces (5003 x 14336, k = 256: 304
+// pieces of 256 KiB, as many bytes written and read again as half of X), and
+// storing those halves in full took 74 us a call against 62.
 constexpr int kSkT = 256;                        // tile edge
 constexpr int kSkSlab = 32;                      // tokens per ring stage
 constexpr int kSkStages = 4;
@@ -411,6 +415,7 @@ struct SkGeom {
     int64_t S;       // 32-token slabs of this launch
     int64_t U;       // units = tiles * S
     int64_t G;       // workgroups
+    int64_t q, r;    // U / G and U % G
     // output addressing (sk_out): matrix mat starts at acc + mat * mbase;
     // element (r, c) lies in diagonal block r >> lsub (lsub = 62 when the
     // matrix is stored whole), which starts bsz floats into the matrix per
@@ -431,7 +436,10 @@ __device__ __forceinline__ int64_t sk_out(const SkGeom& g, int64_t mat, int64_t 
 }
 
 // First unit of workgroup w's share (w = G gives U).
-__device__ __forceinline__ int64_t sk_begin(const SkGeom& g, int64_t w) { return g.U * w / g.G; }
+// floor(U w / G) in 32-bit division (G is at most the device's CU count).
+__device__ __forceinline__ int64_t sk_begin(const SkGeom& g, int64_t w) {
+    return g.q * w + static_cast<uint32_t>(g.r * w) / static_cast<uint32_t>(g.G);
+}
 
 // The k-th upper-triangle tile of a T x T tile grid in super-tile order:
 // 8 x 8 groups of tiles (row-major over the upper triangle of groups),
@@ -743,6 +751,9 @@ __global__ __launch_bounds__(kSkThreads, 1) void cov_sk_kernel(const uint16_t* _
                     // 32 x 32 accumulator lies inside one block)
                     if ((int64_t(wm * 128 + 32 * a) >> g.lsub) != (int64_t(wn * 64 + 32 * b) >> g.lsub))
                         continue;
+                    // of a diagonal tile, the 64 x 64 blocks on and above the
+                    // diagonal (cov_combine_kernel mirrors them)
+                    if (diag && g.lsub == 62 && 2 * wm + a / 2 > wn) continue;
 #pragma unroll
                     for (int r = 0; r < 16; ++r)
                         slot[(rowb + 32 * a + 8 * (r >> 2) + (r & 3)) * kSkT + colb + 32 * b] =
@@ -780,6 +791,10 @@ __global__ __launch_bounds__(kCovThreads) void cov_combine_kernel(float* __restr
     // a packed group's sub-blocks off its block diagonal are not stored
     const int lb = g.lsub > 6 ? g.lsub : 6;
     if ((r0 >> lb) != (c0 >> lb)) return;
+    // a split diagonal tile has its blocks on and above the diagonal only; the
+    // others are written as mirror images (packed groups have both)
+    const bool packed = g.lsub < 62;
+    if (I == J && !packed && sr > sc) return;
     const int64_t w_lo = sk_owner(g, tile * g.S), w_hi = sk_owner(g, (tile + 1) * g.S - 1);
     const bool whole = w_lo == w_hi && sk_begin(g, w_lo) <= tile * g.S &&
                        sk_begin(g, w_lo + 1) >= (tile + 1) * g.S;
@@ -796,39 +811,36 @@ __global__ __launch_bounds__(kCovThreads) void cov_combine_kernel(float* __restr
         v[i] = o[i] >= 0 ? *reinterpret_cast<const f32x4*>(acc + o[i]) : f32x4{0.f, 0.f, 0.f, 0.f};
     }
     if (!whole) {
+        // slot 0 if the tile is the share's first
         auto slot_of = [&](int64_t w) {
-            const int64_t t_first = sk_begin(g, w) / g.S;
-            return ws + (w * 2 + (tile == t_first ? 0 : 1)) * kSkSlotFloats;
+            return ws + (w * 2 + (sk_begin(g, w) >= tile * g.S ? 0 : 1)) * kSkSlotFloats +
+                   (sr + rl) * kSkT + sc + cl;
         };
-        int64_t w = w_lo;
-        // two pieces per round: all their loads in flight before the adds,
-        // which keep the share order
-        for (; w + 1 <= w_hi; w += 2) {
-            const float* s0 = slot_of(w);
-            const float* s1 = slot_of(w + 1);
-            f32x4 p0[4], p1[4];
+        // four pieces per round: all their loads in flight before the adds,
+        // which keep the share order (1024 threads with a unit each instead of
+        // 256 with four: 41 us against 34 at 8192 x 4096, 20 against 16 at 5003
+        // x 14336, k = 256)
+        for (int64_t w = w_lo; w <= w_hi; w += 4) {
+            f32x4 p[4][4];
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                p0[i] = *reinterpret_cast<const f32x4*>(s0 + (sr + rl + 16 * i) * kSkT + sc + cl);
-                p1[i] = *reinterpret_cast<const f32x4*>(s1 + (sr + rl + 16 * i) * kSkT + sc + cl);
+            for (int j = 0; j < 4; ++j) {
+                if (w + j > w_hi) continue;
+                const float* s = slot_of(w + j);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) p[j][i] = *reinterpret_cast<const f32x4*>(s + 16 * i * kSkT);
             }
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                v[i] += p0[i];
-                v[i] += p1[i];
-            }
-        }
-        if (w <= w_hi) {
-            const float* s0 = slot_of(w);
+            for (int j = 0; j < 4; ++j) {
+                if (w + j > w_hi) continue;
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
-                v[i] += *reinterpret_cast<const f32x4*>(s0 + (sr + rl + 16 * i) * kSkT + sc + cl);
+                for (int i = 0; i < 4; ++i) v[i] += p[j][i];
+            }
         }
 #pragma unroll
         for (int i = 0; i < 4; ++i)
             if (o[i] >= 0) *reinterpret_cast<f32x4*>(acc + o[i]) = v[i];
     }
-    if (I == J) return;
+    if (I == J && (packed || sr == sc)) return;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         const int row = rl + 16 * i;
@@ -874,6 +886,10 @@ static bool cov_sk_geometry(int64_t n, int64_t d, int mode, int64_t k, int64_t c
     g.S = (n + kSkSlab - 1) / kSkSlab;
     g.U = g.tiles * g.S;
     g.G = g.U < cus ? g.U : cus;
+    if (g.U > 0) {
+        g.q = g.U / g.G;
+        g.r = g.U % g.G;
+    }
     return g.U > 0;
 }
 
