@@ -1479,7 +1479,8 @@ __global__ __launch_bounds__(kTgThreads, 1) void tq_group_kernel(
     const int64_t cb = gb * 256;                        // first channel of the group
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = threadIdx.x / kWave;
-    auto tile0 = [&](int64_t it) { return (r0 + it * R) * kTgTT; };
+    // pass 2 walks back (see the wide kernel)
+    auto tile0 = [&](int64_t it) { return (r0 + (QUANT ? nt - 1 - it : it) * R) * kTgTT; };
 
     if (wave >= kTgCompute) {
         // ---------------------------------------------------- copy waves
@@ -1692,7 +1693,7 @@ hipError_t launch_tq_group(const uint16_t* X, int64_t n, int64_t d, const uint16
 // leave as 8 bytes per lane, 128 contiguous bytes per token over the 8 waves.
 // Against the kernels that ran these cases before (group kernel up to 256, ring
 // kernel at 512), whole calls, INT4:
-//   16384 x 8192, k = 512   328 -> 241 us (passes 108 and 121 us at best)
+//   16384 x 8192, k = 512   328 -> 253 us (passes 108 and 121 us at best)
 //   4096 x 4096, k = 512     55 -> 38 us (8-bit)
 //   8192 x 14336, k = 256   144 -> 134 us; 300 x 4096 15.8 -> 11.7 us
 //   8192 x 14336, k = 128   112 -> 102 us
@@ -1748,7 +1749,12 @@ __global__ __launch_bounds__(kTwThreads, 1) void tq_wide_kernel(
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const int l32 = lane & 31, h = lane >> 5;
-    auto tile0 = [&](int64_t it) { return (r0 + it * R) * kTwTT; };
+    // Pass 2 walks its tiles from the last to the first: pass 1 left the end of
+    // X in the last-level cache (256 MiB), and walking forward would evict it
+    // before reading it.  Calls with pass 2 forward and back: 16384 x 8192, k =
+    // 512 263 -> 253 us, k = 256 162 -> 149, k = 64 (group kernel) 112 -> 104;
+    // 8192 x 14336, k = 256, 8 bits 144 -> 138; calls whose X is small the same.
+    auto tile0 = [&](int64_t it) { return (r0 + (QUANT ? nt - 1 - it : it) * R) * kTwTT; };
     const int64_t ch = b * KT + half * kTwRows + wave * 32;   // this wave's first channel
     const int xo = (wave * 32 % KT) / K * (K / 8);  // first unit of its block in a tile row
 
