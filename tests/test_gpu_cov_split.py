@@ -5,8 +5,8 @@ blocks, onto a non-zero symmetric start."""
 import numpy as np
 import pytest
 
-from paper_2603_04359_amd import binding as B
 import paper_2603_04359_amd as cat
+from paper_2603_04359_amd import binding as B
 
 from gpu_common import host, say, torch_mod
 
@@ -45,7 +45,7 @@ def test_cov_split_tiles(d, k, n):
     assert bool(((got - got.transpose(1, 2)).abs() <= 2 * bound).all())
 
 
-def test_cov_split_pieces_equal_in_both_orders():
+def test_cov_split_deterministic_and_mirrored():
     """The pieces of a tile are added in one fixed order: two calls agree bit
     for bit, and a diagonal tile's two triangles are mirror images."""
     torch = torch_mod()
