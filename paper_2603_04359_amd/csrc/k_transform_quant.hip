@@ -1697,6 +1697,9 @@ hipError_t launch_tq_group(const uint16_t* X, int64_t n, int64_t d, const uint16
 //   4096 x 4096, k = 512     55 -> 38 us (8-bit)
 //   8192 x 14336, k = 256   144 -> 134 us; 300 x 4096 15.8 -> 11.7 us
 //   8192 x 14336, k = 128   112 -> 102 us
+// workspace offsets (defined with its layout below)
+static size_t tq_twopass_offset(int64_t n, int64_t d);
+static size_t tq_asym_min_offset(int64_t n, int64_t d);
 constexpr int kTwWaves = 8;
 constexpr int kTwThreads = kTwWaves * kWave;
 constexpr int kTwTT = 64;                   // tokens per tile
@@ -1708,7 +1711,7 @@ template <int K, bool QUANT, int QM, bool ASYM>
 __global__ __launch_bounds__(kTwThreads, 1) void tq_wide_kernel(
     const uint16_t* __restrict__ X, const uint16_t* __restrict__ T, int64_t n, int64_t d,
     int64_t R, uint32_t* __restrict__ ws, uint8_t* __restrict__ codes, float* __restrict__ s_x,
-    float* __restrict__ zmin_x) {
+    float* __restrict__ zmin_x, uint64_t* __restrict__ slots, uint64_t* __restrict__ slots_min) {
     static_assert(K == 128 || K == 256 || K == 512, "block size");
     static_assert(!ASYM || QM == 7, "asymmetric codes are INT4");
     constexpr int KT = tw_span(K);                  // channels of a token tile
@@ -1784,7 +1787,7 @@ __global__ __launch_bounds__(kTwThreads, 1) void tq_wide_kernel(
     // minima of asymmetric codes)
     auto copy_words = [&](int64_t it) {
         if constexpr (QUANT) {
-            if (wave < (ASYM ? 2 : 1)) {
+            if (!slots && wave < (ASYM ? 2 : 1)) {
                 const int64_t t0 = tile0(it);
                 const int64_t last = n - 1 - t0;
                 const int j = lane <= last ? lane : static_cast<int>(last);
@@ -1793,6 +1796,26 @@ __global__ __launch_bounds__(kTwThreads, 1) void tq_wide_kernel(
             }
         }
     };
+    // with slots, the row words of all (one or two) tiles now: wave w folds
+    // slots w, w + 8, ...
+    if constexpr (QUANT) {
+        if (slots) {
+            const int64_t nslots = d / kTwRows;
+            for (int i = threadIdx.x; i < 4 * (ASYM ? 2 : 1) * kTwTT; i += kTwThreads) (&words[0][0][0])[i] = 0u;
+            lds_barrier();
+            for (int64_t it = 0; it < nt; ++it) {
+                const int64_t t = tile0(it) + lane < n ? tile0(it) + lane : n - 1;
+                uint32_t m = 0, mn = 0;
+#pragma unroll 4
+                for (int64_t s = wave; s < nslots; s += kTwWaves) {
+                    m = max(m, static_cast<uint32_t>(slots[s * n + t]));
+                    if constexpr (ASYM) mn = max(mn, static_cast<uint32_t>(slots_min[s * n + t]));
+                }
+                atomicMax(&words[it & 3][0][lane], m);
+                if constexpr (ASYM) atomicMax(&words[it & 3][ASYM ? 1 : 0][lane], mn);
+            }
+        }
+    }
     // A operand: row fq_row(l32) of this wave's 32, so that a lane ends up
     // with 16 consecutive channels (16 h ..) of one token.  It comes through
     // the ring, each wave through an eighth of its own and from k = 256 on in
@@ -1834,13 +1857,21 @@ __global__ __launch_bounds__(kTwThreads, 1) void tq_wide_kernel(
         const int64_t t = tile0(it) + lane;
         const uint32_t m = red[p][0][lane];
         red[p][0][lane] = 0u;
+        const int64_t slot = (b * HALVES + half) * n + t;
         if constexpr (ASYM) {
             const uint32_t mn = red[p][1][lane];
             red[p][1][lane] = 0u;
-            if (t < n) {
+            if (slots) {
+                if (t < n) {
+                    slots[slot] = m;
+                    slots_min[slot] = mn;
+                }
+            } else if (t < n) {
                 atomicMax(ws + t, m);
                 atomicMax(ws + n + t, mn);
             }
+        } else if (slots) {
+            if (t < n) slots[slot] = m;
         } else {
             if (t < n && m) atomicMax(ws + t, m);
         }
@@ -2028,14 +2059,29 @@ hipError_t launch_tq_wide(const uint16_t* X, int64_t n, int64_t d, const uint16_
     if (R < 1) R = 1;
     const int64_t units = nb * R;
     const dim3 grid(static_cast<uint32_t>(halves > 1 ? (units + 7) / 8 * 8 * halves : units)), block(kTwThreads);
-    err = launch_fill_zero(ws, ASYM ? 2 * n : n, stream);
-    if (err != hipSuccess) return err;
+    // Calls of one or two tiles per workgroup: pass 1 stores each workgroup's
+    // row words in a slot of its own, and pass 2 folds a token's d / 256 slots
+    // before its first tile, so that nothing has to be cleared (a launch less).
+    // The slots are 64-bit words at the start of the workspace, whose upper
+    // half stays 0: the single pass reads such a word as untagged.
+    // Launch-bound layer calls took 21.1 us with the clearing launch and 17.3
+    // without; 257 x 14336, k = 256 the same (the fold costs what the launch
+    // did), and more tiles would make the fold longer.
+    uint64_t *slots = nullptr, *slots_min = nullptr;
+    if (ntiles <= 2 * R) {
+        uint8_t* const base = reinterpret_cast<uint8_t*>(ws) - tq_twopass_offset(n, d);
+        slots = reinterpret_cast<uint64_t*>(base);
+        if (ASYM) slots_min = reinterpret_cast<uint64_t*>(base + tq_asym_min_offset(n, d));
+    } else {
+        err = launch_fill_zero(ws, ASYM ? 2 * n : n, stream);
+        if (err != hipSuccess) return err;
+    }
     hipLaunchKernelGGL((tq_wide_kernel<K, false, 7, ASYM>), grid, block, 0, stream, X, T, n, d, R, ws,
-                       codes, s_x, zmin_x);
+                       codes, s_x, zmin_x, slots, slots_min);
     err = hipGetLastError();
     if (err != hipSuccess) return err;
     hipLaunchKernelGGL((tq_wide_kernel<K, true, QM, ASYM>), grid, block, 0, stream, X, T, n, d, R, ws,
-                       codes, s_x, zmin_x);
+                       codes, s_x, zmin_x, slots, slots_min);
     return hipGetLastError();
 }
 

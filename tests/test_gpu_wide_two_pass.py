@@ -84,3 +84,32 @@ def test_wide_two_pass_asymmetric(d, k, n):
     q, s, m = _tq_asym(X, T, k, "bf16", "bf16")
     _check_asym(q, s, m, X, T, f"asym d={d} k={k} n={n}")
     assert s[n // 2] == 0 and m[n // 2] == 0 and not q[n // 2].any()
+
+
+# n tokens in one or two tiles per workgroup (row words in slots) against the
+# same tokens at the front of a call with more (row words cleared and folded);
+# on a 256-CU device R = 64 tile rows at d = 1024, 4 at 14336, 8 at 7680 (k = 512)
+@pytest.mark.parametrize("asym", [False, True])
+@pytest.mark.parametrize("d,k,n,more", [(14336, 256, 64 * 8, 600), (14336, 128, 449, 600), (14336, 256, 1, 600),
+                                        (1024, 256, 64 * 128, 64 * 128 + 1), (7680, 512, 64 * 16 - 5, 1100),
+                                        (768, 128, 3, 64 * 200), (14336, 512, 260, 530)])
+def test_wide_two_pass_slots_equal_folded_words(d, k, n, more, asym):
+    torch = torch_mod()
+    say(f"tq wide slots d={d} k={k} n={n} asym={asym}")
+    X, T = _inputs(d, k, more)
+    X[0, :5] = np.inf, -np.inf, 1.0, -1.0, 2.0 ** 127
+    Xd, Td = dev(X, "bf16"), dev(T, "bf16")
+    res = []
+    for m in (n, more):
+        codes = torch.full((m, d // 2), 77, device="cuda", dtype=torch.uint8)
+        s_x, zmin = (torch.full((m,), 5.0, dtype=torch.float32, device="cuda") for _ in range(2))
+        size = cat.cat_transform_quant_asym_workspace_bytes if asym else cat.cat_transform_quant_workspace_bytes
+        ws = torch.full((size(m, d, k),), 0xFF, dtype=torch.uint8, device="cuda")     # no clean workspace needed
+        for _ in range(2):
+            if asym:
+                cat.cat_transform_quant_asym(Xd[:m], Td, k, codes, s_x, zmin, ws)
+            else:
+                cat.cat_transform_quant(Xd[:m], Td, k, codes, s_x, ws)
+        res.append([host(t[:n]).view(np.uint8) for t in (codes, s_x, zmin)])
+    for a, b in zip(*res):
+        assert np.array_equal(a, b)
