@@ -168,7 +168,11 @@ int cat_cov_accumulate(const void* X, int x_dtype, int64_t n, int64_t d,
 size_t cat_transform_quant_workspace_bytes(int64_t n, int64_t d, int64_t k);
 /* Byte offset, inside a workspace of cat_transform_quant_workspace_bytes
  * (n, d, k) bytes, of the exchange timeout word described above (0 when the
- * arguments are invalid). */
+ * arguments are invalid).  The words of all shapes lie in the first 4096
+ * bytes of a workspace, where calls write nothing else but a counter of
+ * theirs, so calls of several shapes may take turns on one workspace and
+ * leave each other's words alone.  Shapes of one width d share a word only
+ * when their n leave the same remainder modulo 331. */
 size_t cat_transform_quant_flag_offset(int64_t n, int64_t d, int64_t k);
 /* Status query for the exchange timeout word (no passage of the paper: a
  * property of this library's single-pass exchange).  Waits for every call
@@ -200,7 +204,7 @@ int cat_transform_quant(const void* X, int x_dtype, int64_t n, int64_t d,
  * device memory (code under HIP graph capture, tight serving loops,
  * harnesses that forbid allocation).  Same arguments, results and errors as
  * cat_transform_quant without the workspace: its scratch is a fixed array
- * of cat_transform_quant_noalloc_max_bytes() bytes (16 MiB) that the
+ * of cat_transform_quant_noalloc_max_bytes() bytes (16 MiB + 3840) that the
  * library holds on each device it runs on, from its first use there until
  * the process ends.  The call allocates nothing and calls no allocating
  * routine.  A call whose cat_transform_quant_workspace_bytes(n, d, k)
@@ -218,7 +222,8 @@ int cat_transform_quant_noalloc(const void* X, int x_dtype, int64_t n, int64_t d
                                 uint8_t* codes, float* s_x, void* stream);
 /* cat_transform_quant_status for the current device's array of
  * cat_transform_quant_noalloc: the timeout word of calls of shape (n, d, k)
- * (each shape has its own word in the array; the array starts zeroed).
+ * (each shape has its word in the array, as in a workspace; the array
+ * starts zeroed).
  * Same returns; CAT_ERR_UNSUPPORTED for a shape the array cannot hold. */
 int cat_transform_quant_noalloc_status(int64_t n, int64_t d, int64_t k, void* stream);
 

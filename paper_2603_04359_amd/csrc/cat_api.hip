@@ -179,10 +179,14 @@ extern "C" int cat_transform_quant(const void* X, int x_dtype, int64_t n, int64_
 // loops).  Each GPU holds its own copy until the process ends; its address
 // on a device is looked up once, with that device current, and kept, and
 // host code only ever hands that address on.  The transform+quant paths
-// clear what they need cleared with their own kernels (the two-pass maxima)
-// or need nothing cleared (the tagged single-pass words), so the contents a
-// previous call left are harmless; calls that overlap on one GPU race.
-constexpr size_t kScratchBytes = size_t{16} << 20;
+// clear what they need cleared with their own kernels (the two-pass maxima),
+// write every word they read (the wide kernel's slots) or need nothing
+// cleared (the tagged single-pass words), so the contents a previous call of
+// any shape left are harmless; calls that overlap on one GPU race.  The
+// timeout words of all shapes lie in the workspace's head, which only they
+// and the tag of captured calls use: 4096 bytes, of which 3840 are on top of
+// the 16 MiB.
+constexpr size_t kScratchBytes = (size_t{16} << 20) + 3840;
 static __device__ __align__(256) uint8_t scratch[kScratchBytes];
 
 namespace {

@@ -24,7 +24,8 @@
 //     pass 2 (quant) recomputes z with the identical instruction sequence,
 //                   reads the finished row maximum and writes packed codes.
 //   A fill kernel clears the per-token words first (no hipMemset, so the
-//   sequence can be captured in a graph);
+//   sequence can be captured in a graph), except where the wide kernel's
+//   workgroups store theirs apart (its slots);
 //   whole rows      (fp32 operands and other bf16 blocks of at least 16,
 //                   d <= 4096; tq_rows_kernel) one launch, a workgroup holds
 //                   the whole rows of 16 tokens.
@@ -825,9 +826,9 @@ __global__ __launch_bounds__(kTqThreads, 2) void tq_ring_kernel(
 // P words).  A word is
 // (call tag << 32) | maximum bits written with one store, so a reader sees
 // either an old word (another tag) or the whole new one and the workspace
-// needs no clearing between calls.  Tags have bit 31 set; the two-pass
-// paths keep their words in a region of the workspace of their own, so
-// nothing they leave behind is read here.  Eager calls take the tag from a host
+// needs no clearing between calls.  Tags have bit 31 set; what the two-pass
+// paths and calls of other shapes leave in these words never carries the
+// call's tag (see the workspace layout).  Eager calls take the tag from a host
 // counter; a call captured into a graph takes it from a word a one-thread
 // kernel advances before every replay (see launch_tq_fused).  P(j, t) lives at
 // ((t / 16) * NB + j) * 16 + t % 16 (16 tokens of a block fill one 128-byte
@@ -1698,6 +1699,7 @@ hipError_t launch_tq_group(const uint16_t* X, int64_t n, int64_t d, const uint16
 //   8192 x 14336, k = 256   144 -> 134 us; 300 x 4096 15.8 -> 11.7 us
 //   8192 x 14336, k = 128   112 -> 102 us
 // workspace offsets (defined with its layout below)
+constexpr size_t kTqHeadBytes = 4096;
 static size_t tq_twopass_offset(int64_t n, int64_t d);
 static size_t tq_asym_min_offset(int64_t n, int64_t d);
 constexpr int kTwWaves = 8;
@@ -2062,15 +2064,15 @@ hipError_t launch_tq_wide(const uint16_t* X, int64_t n, int64_t d, const uint16_
     // Calls of one or two tiles per workgroup: pass 1 stores each workgroup's
     // row words in a slot of its own, and pass 2 folds a token's d / 256 slots
     // before its first tile, so that nothing has to be cleared (a launch less).
-    // The slots are 64-bit words at the start of the workspace, whose upper
-    // half stays 0: the single pass reads such a word as untagged.
+    // The slots are 64-bit words in the exchange region, whose upper half
+    // stays 0: the single pass reads such a word as untagged.
     // Launch-bound layer calls took 21.1 us with the clearing launch and 17.3
     // without; 257 x 14336, k = 256 the same (the fold costs what the launch
     // did), and more tiles would make the fold longer.
     uint64_t *slots = nullptr, *slots_min = nullptr;
     if (ntiles <= 2 * R) {
         uint8_t* const base = reinterpret_cast<uint8_t*>(ws) - tq_twopass_offset(n, d);
-        slots = reinterpret_cast<uint64_t*>(base);
+        slots = reinterpret_cast<uint64_t*>(base + kTqHeadBytes);
         if (ASYM) slots_min = reinterpret_cast<uint64_t*>(base + tq_asym_min_offset(n, d));
     } else {
         err = launch_fill_zero(ws, ASYM ? 2 * n : n, stream);
@@ -2131,30 +2133,43 @@ hipError_t launch_tq_ring(const uint16_t* X, int64_t n, int64_t d, const uint16_
     return hipGetLastError();
 }
 
-// Workspace layout (bytes): [0, P) the single-pass exchange words (d/128
-// 64-bit tagged block maxima and one tagged row maximum per token, n
-// rounded up to 16, P = 8 n' (max(1, d / 128) + 1)); then a 256-byte tail:
-// the 32-bit timeout flag at +0 and the device-side tag of captured calls
-// at +64; then 8 n bytes for the two-pass paths (one 32-bit running
-// maximum per token, or the asymmetric path's two 32-bit keys per token).
-// The two regions never overlap, so words one path leaves behind are never
-// read by the other: the asymmetric keys can have bit 31 set and could
-// otherwise pass for a tagged word.  The asymmetric entry point's workspace
-// adds a third region (see tq_asym_min_offset).
+// Workspace layout (bytes):
+//   [0, 4096)   the head: the device-side tag of captured calls at 0 and the
+//               timeout words from 64 on.  It lies at the same place whatever
+//               the shape and nothing else is ever written to it, so that calls
+//               of several shapes can share a workspace (as they share the
+//               scratch array): a place that depended on the shape would be
+//               inside another shape's regions.
+//   [4096, + P) the exchange region, P = 8 n' (max(1, d / 128) + 1), n' = n
+//               rounded up to 16: the single pass's tagged words (d / 128
+//               block maxima and one row maximum per token), or the wide
+//               kernel's slots (d / 256 words per token, upper half 0).
+//   8 n bytes   the other two-pass kernels' words: one 32-bit running maximum
+//               per token, or the asymmetric path's two 32-bit keys.
+//   P bytes     (asymmetric entry point only) the minimum keys' exchange
+//               region, laid out like the maximum keys'.
+// What a call finds in its regions is its own only where it wrote it: the
+// two-pass paths clear or write every word they read, and the single pass
+// takes a word for its own only if it carries the call's tag.
 static int64_t tq_nbj_max(int64_t d) { return d / 128 > 1 ? d / 128 : 1; }
-static size_t tq_flag_offset(int64_t n, int64_t d) {
+static size_t tq_exchange_bytes(int64_t n, int64_t d) {
     return static_cast<size_t>((n + 15) / 16 * 16 * 8 * (tq_nbj_max(d) + 1));
 }
-static size_t tq_twopass_offset(int64_t n, int64_t d) { return tq_flag_offset(n, d) + 256; }
-// asymmetric single pass: the minimum keys' P and F words, laid out like the
-// maximum keys', after the two-pass region
+// A timeout word per shape: the three single-pass widths never share one,
+// shapes of a width do when their n agree modulo a prime.
+static size_t tq_flag_offset(int64_t n, int64_t d) {
+    constexpr int64_t kPrime = 331;
+    static_assert(64 + 4 * 3 * kPrime <= kTqHeadBytes, "timeout words fit the head");
+    return static_cast<size_t>(64 + 4 * (n % kPrime * 3 + (d == 4096 ? 1 : d == 8192 ? 2 : 0)));
+}
+static size_t tq_twopass_offset(int64_t n, int64_t d) { return kTqHeadBytes + tq_exchange_bytes(n, d); }
 static size_t tq_asym_min_offset(int64_t n, int64_t d) {
     return tq_twopass_offset(n, d) + static_cast<size_t>(n) * 8;
 }
 size_t tq_asym_workspace_bytes(int64_t n, int64_t d, int64_t k) {
     (void)k;
     if (n < 1) return 0;
-    return tq_asym_min_offset(n, d) + tq_flag_offset(n, d);
+    return tq_asym_min_offset(n, d) + tq_exchange_bytes(n, d);
 }
 size_t tq_flag_offset_bytes(int64_t n, int64_t d) { return tq_flag_offset(n, d); }
 size_t tq_workspace_bytes(int64_t n, int64_t d, int64_t k) {
@@ -2213,7 +2228,7 @@ static hipError_t launch_tq_fused_nb(const uint16_t* X, int64_t n, int64_t d, co
     if (R > ntiles) R = ntiles;
     if (R < 1) R = 1;
     TqFusedWs w;
-    w.pmax = reinterpret_cast<uint64_t*>(ws);
+    w.pmax = reinterpret_cast<uint64_t*>(ws + kTqHeadBytes);
     w.pmin = ASYM ? reinterpret_cast<uint64_t*>(ws + tq_asym_min_offset(n, d)) : nullptr;
     w.flag = reinterpret_cast<uint32_t*>(ws + tq_flag_offset(n, d));
     w.tag_word = nullptr;
@@ -2223,8 +2238,8 @@ static hipError_t launch_tq_fused_nb(const uint16_t* X, int64_t n, int64_t d, co
     if (err != hipSuccess) return err;
     if (capture != hipStreamCaptureStatusNone) {
         // captured: the tag has to change with every replay, so it is made
-        // on the device, in the workspace tail next to the timeout flag
-        uint32_t* word = reinterpret_cast<uint32_t*>(ws + tq_flag_offset(n, d) + 64);
+        // on the device, in the first word of the workspace's head
+        uint32_t* word = reinterpret_cast<uint32_t*>(ws);
         hipLaunchKernelGGL(tq_device_tag_kernel, dim3(1), dim3(kWave), 0, stream, word);
         err = hipGetLastError();
         if (err != hipSuccess) return err;
