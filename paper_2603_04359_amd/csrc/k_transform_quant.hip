@@ -55,15 +55,21 @@ constexpr float kQmax4 = 7.0f;
 constexpr int64_t kTqTargetWorkgroups = 512;
 
 __global__ void fill_zero_u32_kernel(uint32_t* p, int64_t n) {
-    const int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (i < n) p[i] = 0u;
+    const int64_t step = static_cast<int64_t>(gridDim.x) * blockDim.x;
+    for (int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x; i < n; i += step) p[i] = 0u;
 }
 // The two-pass paths clear their per-token words first.
 static hipError_t launch_fill_zero(uint32_t* p, int64_t n, hipStream_t stream) {
-    hipLaunchKernelGGL(fill_zero_u32_kernel, dim3(static_cast<uint32_t>((n + 255) / 256)), dim3(256),
-                       0, stream, p, n);
+    const int64_t blocks = (n + 255) / 256;
+    hipLaunchKernelGGL(fill_zero_u32_kernel, dim3(static_cast<uint32_t>(blocks < (1 << 22) ? blocks : 1 << 22)),
+                       dim3(256), 0, stream, p, n);
     return hipGetLastError();
 }
+// Asymmetric codes: the 32-bit words of token t's maximum and minimum keys
+// among the two-pass words ws.  Each is the lower half of a 64-bit word whose
+// upper half stays 0 (see the workspace layout).
+__device__ __forceinline__ int64_t max_key(int64_t t) { return 2 * t; }
+__device__ __forceinline__ int64_t min_key(int64_t n, int64_t t) { return 2 * (n + t); }
 
 // Quantize one value given inv = qmax/amax (amax > 0); returns the code
 // in [-qmax, qmax] as an int.
@@ -179,8 +185,8 @@ __global__ __launch_bounds__(kTqThreads) void tq_generic_minmax_kernel(
     const int64_t c = 2 * (u - t * pairs);
     const uint32_t k0 = fkey(tq_dot(X, T, t, d, k, c));
     const uint32_t k1 = fkey(tq_dot(X, T, t, d, k, c + 1));
-    atomicMax(ws + t, max(k0, k1));
-    atomicMax(ws + n + t, max(~k0, ~k1));
+    atomicMax(ws + max_key(t), max(k0, k1));
+    atomicMax(ws + min_key(n, t), max(~k0, ~k1));
 }
 
 template <typename XT, typename TT>
@@ -194,7 +200,7 @@ __global__ __launch_bounds__(kTqThreads) void tq_generic_quant_asym_kernel(
     const int64_t t = u / pairs;
     const int64_t cp = u - t * pairs;
     float zmin, s, inv;
-    asym_scale(ws[t], ws[n + t], zmin, s, inv);
+    asym_scale(ws[max_key(t)], ws[min_key(n, t)], zmin, s, inv);
     if (cp == 0) {
         s_x[t] = s;
         zmin_x[t] = zmin;
@@ -667,8 +673,8 @@ __global__ __launch_bounds__(kTqThreads, 2) void tq_ring_kernel(
                 const uint32_t mn = max(max(red[4][idx], red[5][idx]), max(red[6][idx], red[7][idx]));
                 const int64_t t = tile * C::TT + idx;
                 if (t < n) {
-                    atomicMax(amax_ws + t, mx);
-                    atomicMax(amax_ws + n + t, mn);
+                    atomicMax(amax_ws + max_key(t), mx);
+                    atomicMax(amax_ws + min_key(n, t), mn);
                 }
             }
         } else if constexpr (ASYM) {
@@ -678,7 +684,7 @@ __global__ __launch_bounds__(kTqThreads, 2) void tq_ring_kernel(
                 const int64_t t = tile * C::TT + sb * 32 + l32;
                 const bool valid = t < n;
                 float zmin = 0.0f, s = 0.0f, inv = 0.0f;
-                if (valid) asym_scale(amax_ws[t], amax_ws[n + t], zmin, s, inv);
+                if (valid) asym_scale(amax_ws[max_key(t)], amax_ws[min_key(n, t)], zmin, s, inv);
                 if (valid && h == 0 && wave == 0 && b == 0 && jc == 0) {
                     s_x[t] = s;
                     zmin_x[t] = zmin;
@@ -1452,8 +1458,8 @@ __device__ __forceinline__ void tg_wait_copies(int later) {
 }
 
 
-// QUANT false: pass 1 (row maxima into ws[t], or for ASYM the max key into
-// ws[t] and the complemented min key into ws[n + t]).  QUANT true: pass 2
+// QUANT false: pass 1 (row maxima into ws[t], or for ASYM the max key and the
+// complemented min key into their words).  QUANT true: pass 2
 // (codes and s_x from the finished words; for ASYM also zmin_x).
 template <int K, bool QUANT, int QM, bool ASYM>
 __global__ __launch_bounds__(kTgThreads, 1) void tq_group_kernel(
@@ -1505,8 +1511,8 @@ __global__ __launch_bounds__(kTgThreads, 1) void tq_group_kernel(
                 // asymmetric: wave 0 the max keys, wave 1 the min keys
                 int j = ASYM ? lane : cw * 32 + (lane & 31);
                 j = j <= last ? j : static_cast<int>(last);
-                const uint32_t* src = ws + (ASYM && cw ? n : 0) + t0;
-                dma4(src, static_cast<uint32_t>(j * 4), lds_addr(&words[st][cw * 64]));
+                const uint32_t* src = ws + (!ASYM ? t0 : cw ? min_key(n, t0) : max_key(t0));
+                dma4(src, static_cast<uint32_t>(j * (ASYM ? 8 : 4)), lds_addr(&words[st][cw * 64]));
             }
         };
         for (int64_t it = 0; it < nt && it < kTgAhead; ++it) issue(it);
@@ -1552,8 +1558,8 @@ __global__ __launch_bounds__(kTgThreads, 1) void tq_group_kernel(
             const uint32_t mn = red[p][1][j];
             red[p][1][j] = 0u;
             if (t < n) {
-                atomicMax(ws + t, m);
-                atomicMax(ws + n + t, mn);
+                atomicMax(ws + max_key(t), m);
+                atomicMax(ws + min_key(n, t), mn);
             }
         } else {
             if (t < n && m) atomicMax(ws + t, m);
@@ -1667,7 +1673,7 @@ hipError_t launch_tq_group(const uint16_t* X, int64_t n, int64_t d, const uint16
     if (R > ntiles) R = ntiles;
     if (R < 1) R = 1;
     const dim3 grid(static_cast<uint32_t>(ngroups * R)), block(kTgThreads);
-    err = launch_fill_zero(ws, ASYM ? 2 * n : n, stream);
+    err = launch_fill_zero(ws, ASYM ? 4 * n : n, stream);
     if (err != hipSuccess) return err;
     hipLaunchKernelGGL((tq_group_kernel<K, false, 7, ASYM>), grid, block, 0, stream, X, T, n, d, R,
                        ws, codes, s_x, zmin_x);
@@ -1793,7 +1799,7 @@ __global__ __launch_bounds__(kTwThreads, 1) void tq_wide_kernel(
                 const int64_t t0 = tile0(it);
                 const int64_t last = n - 1 - t0;
                 const int j = lane <= last ? lane : static_cast<int>(last);
-                dma4(ws + (wave ? n : 0) + t0, static_cast<uint32_t>(j * 4),
+                dma4(ws + (!ASYM ? t0 : wave ? min_key(n, t0) : max_key(t0)), static_cast<uint32_t>(j * (ASYM ? 8 : 4)),
                      lds_addr(&words[it & 3][ASYM ? wave : 0][0]));
             }
         }
@@ -1869,8 +1875,8 @@ __global__ __launch_bounds__(kTwThreads, 1) void tq_wide_kernel(
                     slots_min[slot] = mn;
                 }
             } else if (t < n) {
-                atomicMax(ws + t, m);
-                atomicMax(ws + n + t, mn);
+                atomicMax(ws + max_key(t), m);
+                atomicMax(ws + min_key(n, t), mn);
             }
         } else if (slots) {
             if (t < n) slots[slot] = m;
@@ -2075,7 +2081,7 @@ hipError_t launch_tq_wide(const uint16_t* X, int64_t n, int64_t d, const uint16_
         slots = reinterpret_cast<uint64_t*>(base + kTqHeadBytes);
         if (ASYM) slots_min = reinterpret_cast<uint64_t*>(base + tq_asym_min_offset(n, d));
     } else {
-        err = launch_fill_zero(ws, ASYM ? 2 * n : n, stream);
+        err = launch_fill_zero(ws, ASYM ? 4 * n : n, stream);
         if (err != hipSuccess) return err;
     }
     hipLaunchKernelGGL((tq_wide_kernel<K, false, 7, ASYM>), grid, block, 0, stream, X, T, n, d, R, ws,
@@ -2122,7 +2128,7 @@ hipError_t launch_tq_ring(const uint16_t* X, int64_t n, int64_t d, const uint16_
     if (err != hipSuccess) return err;
     int64_t R = 0;
     const int64_t grid = tq_ring_grid<K>(n, d, cus, R);
-    err = launch_fill_zero(ws, ASYM ? 2 * n : n, stream);
+    err = launch_fill_zero(ws, ASYM ? 4 * n : n, stream);
     if (err != hipSuccess) return err;
     hipLaunchKernelGGL((tq_ring_kernel<K, false, 7, ASYM>), dim3(static_cast<uint32_t>(grid)),
                        dim3(kTqThreads), 0, stream, X, T, n, d, R, ws, codes, s_x, zmin_x);
@@ -2145,12 +2151,17 @@ hipError_t launch_tq_ring(const uint16_t* X, int64_t n, int64_t d, const uint16_
 //               block maxima and one row maximum per token), or the wide
 //               kernel's slots (d / 256 words per token, upper half 0).
 //   8 n bytes   the other two-pass kernels' words: one 32-bit running maximum
-//               per token, or the asymmetric path's two 32-bit keys.
+//               per token (symmetric codes), or the maximum keys.
 //   P bytes     (asymmetric entry point only) the minimum keys' exchange
-//               region, laid out like the maximum keys'.
+//               region, laid out like the maximum keys'; the two-pass
+//               kernels' minimum keys at its start (8 n bytes).
 // What a call finds in its regions is its own only where it wrote it: the
 // two-pass paths clear or write every word they read, and the single pass
-// takes a word for its own only if it carries the call's tag.
+// takes a 64-bit word for its own only if its upper half is the call's tag,
+// which has bit 31 set.  No call leaves a word with that bit set that is not
+// a tagged one: maxima of symmetric codes are bits of non-negative floats,
+// and a key, which can be any 32 bits (2.0 + c ulp has the key of device tag
+// c), is the lower half of a word with a zero upper half.
 static int64_t tq_nbj_max(int64_t d) { return d / 128 > 1 ? d / 128 : 1; }
 static size_t tq_exchange_bytes(int64_t n, int64_t d) {
     return static_cast<size_t>((n + 15) / 16 * 16 * 8 * (tq_nbj_max(d) + 1));
@@ -2361,7 +2372,7 @@ static hipError_t launch_tq_generic_asym(const XT* X, int64_t n, int64_t d, cons
                                          uint32_t* ws, hipStream_t stream) {
     if (tq_rows_fits(d, k))
         return launch_tq_rows<7, true>(X, n, d, T, k, codes, s_x, zmin_x, stream);
-    hipError_t err = launch_fill_zero(ws, 2 * n, stream);
+    hipError_t err = launch_fill_zero(ws, 4 * n, stream);
     if (err != hipSuccess) return err;
     const int64_t units = n * (d / 2);
     const int64_t grid = (units + kTqThreads - 1) / kTqThreads;

@@ -142,3 +142,23 @@ def test_replays_of_two_shapes_on_one_workspace(asym):
                 else:
                     check_codes(c, Xs[i], Ts[i], label=f"replay {rep}, call {i}")
         cat.cat_transform_quant_status(ws, *shapes[0])
+
+
+# every two-pass route: slots, wide, group, ring, whole-key vector ALU, mfma
+@pytest.mark.gpu
+@pytest.mark.parametrize("n,d,k,dtype", [
+    (257, 14336, 256, "bf16"), (3000, 14336, 128, "bf16"), (300, 4096, 64, "bf16"), (64, 1024, 512, "bf16"),
+    (100, 640, 128, "bf16"), (100, 96, 32, "bf16"), (30, 4352, 64, "f32"), (40, 64, 8, "f32")])
+@pytest.mark.parametrize("asym", [True, False])
+def test_two_pass_words_carry_no_tag(n, d, k, dtype, asym):
+    # a single-pass call of another shape on the workspace takes a 64-bit word
+    # whose upper half is its tag (bit 31 set) for a published one
+    say(f"tq two-pass words {n} x {d}, k={k} {dtype} asym={asym}")
+    torch = torch_mod()
+    size = cat.cat_transform_quant_asym_workspace_bytes if asym else cat.cat_transform_quant_workspace_bytes
+    ws = torch.zeros(size(n, d, k), dtype=torch.uint8, device="cuda")
+    run, _ = _call(dev(_wide_X(n, d, seed=70), dtype), dev(_rand_T(d, k, seed=71), dtype), k, ws, asym)
+    run()
+    words = host(ws)
+    assert not words[:HEAD].any()
+    assert (words[HEAD:].view(np.int64) >= 0).all()
