@@ -1712,6 +1712,7 @@ constexpr int kTwWaves = 8;
 constexpr int kTwThreads = kTwWaves * kWave;
 constexpr int kTwTT = 64;                   // tokens per tile
 constexpr int kTwRows = 256;                // output rows per workgroup
+constexpr int kTwTwoTileSlots = 8;          // slots of a row up to which two tiles take slots
 // channels of X that a workgroup's rows read: 256 / k blocks, or one of 512
 constexpr int tw_span(int k) { return k < 256 ? 256 : k; }
 
@@ -2067,16 +2068,20 @@ hipError_t launch_tq_wide(const uint16_t* X, int64_t n, int64_t d, const uint16_
     if (R < 1) R = 1;
     const int64_t units = nb * R;
     const dim3 grid(static_cast<uint32_t>(halves > 1 ? (units + 7) / 8 * 8 * halves : units)), block(kTwThreads);
-    // Calls of one or two tiles per workgroup: pass 1 stores each workgroup's
-    // row words in a slot of its own, and pass 2 folds a token's d / 256 slots
-    // before its first tile, so that nothing has to be cleared (a launch less).
-    // The slots are 64-bit words in the exchange region, whose upper half
-    // stays 0: the single pass reads such a word as untagged.
-    // Launch-bound layer calls took 21.1 us with the clearing launch and 17.3
-    // without; 257 x 14336, k = 256 the same (the fold costs what the launch
-    // did), and more tiles would make the fold longer.
+    // Calls of one tile per workgroup (of two where the row is narrow), with
+    // all workgroups resident at once: pass 1 stores each workgroup's row words
+    // in a slot of its own, and pass 2 folds a token's d / 256 slots before its
+    // first tile, so that nothing has to be cleared (a launch less).  The slots
+    // are 64-bit words in the exchange region, whose upper half stays 0: the
+    // single pass reads such a word as untagged.
+    // One tile: 1 x 14336, k = 128 13.4 us with the clearing launch and 11.2
+    // without, 64 x 65536 19.2 and 16.6; two: 4096 x 1280 13.7 and 12.5, but
+    // 300 x 14336 14.4 and 15.0, 1000 x 6144 (asymmetric) 16.0 and 16.8; two
+    // rounds of workgroups fold one after the other: 64 x 131072, k = 256 41.8
+    // and 46.8.
+    const bool one_round = nb * halves <= cus;
     uint64_t *slots = nullptr, *slots_min = nullptr;
-    if (ntiles <= 2 * R) {
+    if (one_round && (ntiles <= R || (ntiles <= 2 * R && d <= kTwTwoTileSlots * kTwRows))) {
         uint8_t* const base = reinterpret_cast<uint8_t*>(ws) - tq_twopass_offset(n, d);
         slots = reinterpret_cast<uint64_t*>(base + kTqHeadBytes);
         if (ASYM) slots_min = reinterpret_cast<uint64_t*>(base + tq_asym_min_offset(n, d));

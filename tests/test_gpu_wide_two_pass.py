@@ -86,8 +86,9 @@ def test_wide_two_pass_asymmetric(d, k, n):
     assert s[n // 2] == 0 and m[n // 2] == 0 and not q[n // 2].any()
 
 
-# n tokens in one or two tiles per workgroup (row words in slots) against the
-# same tokens at the front of a call with more (row words cleared and folded);
+# n tokens in one tile per workgroup (two up to d = 2048; row words in slots)
+# or in two or three (row words cleared and folded) against the same tokens at
+# the front of a call with more;
 # on a 256-CU device R = 64 tile rows at d = 1024, 4 at 14336, 8 at 7680 (k = 512)
 @pytest.mark.parametrize("asym", [False, True])
 @pytest.mark.parametrize("d,k,n,more", [(14336, 256, 64 * 8, 600), (14336, 128, 449, 600), (14336, 256, 1, 600),
