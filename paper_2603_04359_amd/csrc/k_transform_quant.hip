@@ -30,8 +30,9 @@
 //                   d <= 4096; tq_rows_kernel) one launch, a workgroup holds
 //                   the whole rows of 16 tokens.
 // Two-pass kernels, by case: tq_wide_kernel (bf16, k = 128, 256, 512, d a
-// multiple of 256), tq_group_kernel (bf16, k = 32, 64, d a multiple of 256),
-// tq_ring_kernel (bf16 k = 128 otherwise, and k = 512 for few tokens),
+// multiple of 256), tq_group_kernel (bf16, k = 32, 64, d a multiple of 256, and
+// large calls at k = 128 or on very wide rows), tq_ring_kernel (bf16 k = 128 otherwise, and k = 512
+// for few tokens),
 // tq_mfma_kernel (bf16 k = 32, 64 otherwise) and the vector-ALU kernels (the
 // rest).  The asymmetric INT4 variant takes the same routes with a row maximum
 // and minimum, except that bf16 k = 32 and 64 off the group kernel's widths go
@@ -1418,7 +1419,7 @@ __global__ __launch_bounds__(kFqThreads, 1) void tq_fused_kernel(
 }
 
 // ------------------------------------------------ group two-pass path
-// bf16, k = 32 or 64 with d a multiple of 256.  One persistent
+// bf16, k = 32, 64, 128 or 256 with d a multiple of 256.  One persistent
 // workgroup per CU owns a group of 256 channels (one or more whole blocks)
 // for the token tiles r, r + R, ...  Six waves with fixed roles:
 //   waves 0-3  compute: wave w holds rows 64 w .. + 63 of the group's T
@@ -1435,8 +1436,8 @@ __global__ __launch_bounds__(kFqThreads, 1) void tq_fused_kernel(
 // Pass 1 folds per-token maxima of the four waves with LDS atomics; the
 // tile's maxima go to the global per-token words one step later (after the
 // next barrier), which needs no barrier of its own.
-// (Larger blocks run on the wide kernel below, which measured 3-20% faster
-// there and the same at k = 32 and 64.)
+// (Calls at k = 128 and 256 that the rules tq_wide_128 and tq_wide_256 name run
+// on the wide kernel below; k = 32 and 64 measured the same there.)
 constexpr int kTgCompute = 4;
 constexpr int kTgCopy = 2;
 constexpr int kTgThreads = (kTgCompute + kTgCopy) * kWave;
@@ -1466,7 +1467,7 @@ __global__ __launch_bounds__(kTgThreads, 1) void tq_group_kernel(
     const uint16_t* __restrict__ X, const uint16_t* __restrict__ T, int64_t n, int64_t d,
     int64_t R, uint32_t* __restrict__ ws, uint8_t* __restrict__ codes, float* __restrict__ s_x,
     float* __restrict__ zmin_x) {
-    static_assert(K == 32 || K == 64, "block size");
+    static_assert(K == 32 || K == 64 || K == 128 || K == 256, "block size");
     constexpr int NS = K / 16;                          // 16-deep MFMA steps
     constexpr int NSB = kTgTT / 32;                     // 32-token subtiles
     constexpr bool kShare = K >= 64;                    // both row groups in one block
@@ -1658,13 +1659,8 @@ __global__ __launch_bounds__(kTgThreads, 1) void tq_group_kernel(
 
 template <int K, int QM, bool ASYM = false>
 hipError_t launch_tq_group(const uint16_t* X, int64_t n, int64_t d, const uint16_t* T,
-                           uint8_t* codes, float* s_x, uint32_t* ws, hipStream_t stream,
+                           uint8_t* codes, float* s_x, uint32_t* ws, int64_t cus, hipStream_t stream,
                            float* zmin_x = nullptr) {
-    int dev = 0, cus = 0;
-    hipError_t err = hipGetDevice(&dev);
-    if (err != hipSuccess) return err;
-    err = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-    if (err != hipSuccess) return err;
     const int64_t ntiles = (n + kTgTT - 1) / kTgTT;
     const int64_t ngroups = d / 256;
     // one workgroup per CU: R token-tile rows per channel group, rounded
@@ -1673,7 +1669,7 @@ hipError_t launch_tq_group(const uint16_t* X, int64_t n, int64_t d, const uint16
     if (R > ntiles) R = ntiles;
     if (R < 1) R = 1;
     const dim3 grid(static_cast<uint32_t>(ngroups * R)), block(kTgThreads);
-    err = launch_fill_zero(ws, ASYM ? 4 * n : n, stream);
+    hipError_t err = launch_fill_zero(ws, ASYM ? 4 * n : n, stream);
     if (err != hipSuccess) return err;
     hipLaunchKernelGGL((tq_group_kernel<K, false, 7, ASYM>), grid, block, 0, stream, X, T, n, d, R,
                        ws, codes, s_x, zmin_x);
@@ -1700,10 +1696,11 @@ hipError_t launch_tq_group(const uint16_t* X, int64_t n, int64_t d, const uint16
 // leave as 8 bytes per lane, 128 contiguous bytes per token over the 8 waves.
 // Against the kernels that ran these cases before (group kernel up to 256, ring
 // kernel at 512), whole calls, INT4:
-//   16384 x 8192, k = 512   328 -> 253 us (passes 108 and 121 us at best)
-//   4096 x 4096, k = 512     55 -> 38 us (8-bit)
-//   8192 x 14336, k = 256   144 -> 134 us; 300 x 4096 15.8 -> 11.7 us
-//   8192 x 14336, k = 128   112 -> 102 us
+//   16384 x 8192, k = 512   340 -> 243 us (passes 108 and 121 us at best)
+//   4096 x 4096, k = 512     55 -> 40 us
+//   4096 x 14336, k = 256    78 -> 73 us, asymmetric 99 -> 83; 8192 tokens 137
+//                           and 136; 300 x 4096 16.5 -> 11.3 us
+//   4096 x 1280, k = 128    16.1 -> 12.3 us
 // workspace offsets (defined with its layout below)
 constexpr size_t kTqHeadBytes = 4096;
 static size_t tq_twopass_offset(int64_t n, int64_t d);
@@ -2053,12 +2050,7 @@ __global__ __launch_bounds__(kTwThreads, 1) void tq_wide_kernel(
 
 template <int K, int QM, bool ASYM = false>
 hipError_t launch_tq_wide(const uint16_t* X, int64_t n, int64_t d, const uint16_t* T, uint8_t* codes,
-                          float* s_x, uint32_t* ws, hipStream_t stream, float* zmin_x = nullptr) {
-    int dev = 0, cus = 0;
-    hipError_t err = hipGetDevice(&dev);
-    if (err != hipSuccess) return err;
-    err = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-    if (err != hipSuccess) return err;
+                          float* s_x, uint32_t* ws, int64_t cus, hipStream_t stream, float* zmin_x = nullptr) {
     constexpr int64_t halves = tw_span(K) / kTwRows;
     const int64_t nb = d / tw_span(K), ntiles = (n + kTwTT - 1) / kTwTT;
     // one workgroup per CU: R token-tile rows, rounded down so that every
@@ -2080,6 +2072,7 @@ hipError_t launch_tq_wide(const uint16_t* X, int64_t n, int64_t d, const uint16_
     // rounds of workgroups fold one after the other: 64 x 131072, k = 256 41.8
     // and 46.8.
     const bool one_round = nb * halves <= cus;
+    hipError_t err = hipSuccess;
     uint64_t *slots = nullptr, *slots_min = nullptr;
     if (one_round && (ntiles <= R || (ntiles <= 2 * R && d <= kTwTwoTileSlots * kTwRows))) {
         uint8_t* const base = reinterpret_cast<uint8_t*>(ws) - tq_twopass_offset(n, d);
@@ -2098,13 +2091,40 @@ hipError_t launch_tq_wide(const uint16_t* X, int64_t n, int64_t d, const uint16_
     return hipGetLastError();
 }
 
-// The group (k = 32, 64) and wide (k = 128, 256, 512) kernels take whole spans.
+// The group (k = 32 to 256) and wide (k = 128, 256, 512) kernels take whole
+// spans.
 static bool tq_spans_fit(int64_t d, int64_t k) { return k >= 32 && d % tw_span(static_cast<int>(k)) == 0; }
+// Whether a k = 128 call runs on the wide kernel: where each of its workgroups
+// has one tile, or several workgroups share a span and X is small.  Otherwise
+// the group kernel, whose copy waves keep more of X in flight, streams it
+// faster: 8192 x 14336 100-103 us against 109-111 (16384 tokens 203 and 225),
+// 128 x 65536 21.0 and 22.7, 64 x 131072 29.8 and 31.5; in between they
+// measure alike (2048 x 14336 32.2 and 32.3, 4096 x 10240 41.3 and 42.6), and
+// small calls are faster here (8192 x 1280 17.5 us against 19.0).
+static bool tq_wide_128(int64_t n, int64_t d, int64_t cus) {
+    const int64_t nb = d / kTwRows, ntiles = (n + kTwTT - 1) / kTwTT;
+    return nb <= cus && (ntiles <= cus / nb || (2 * nb <= cus && n * d < int64_t{1} << 25));
+}
+// At k = 256 the group kernel is the better one only for a few tiles of rows so
+// wide that a CU has one span or more to itself: 65 x 65536 22.8 us and 26.9,
+// 64 x 131072 41.4 and 46.6, 300 x 65536 41.8 and 41.7, 1000 x 65536
+// (asymmetric) 107 and 99.
+static bool tq_wide_256(int64_t n, int64_t d, int64_t cus) {
+    const int64_t nb = d / kTwRows;
+    return nb < cus || n > 4 * kTwTT || (nb == cus && n <= kTwTT);
+}
 // At k = 512 a call of few tiles is all ramp, and the ring kernel's workgroups
 // load half as much of T: 64 x 1024 took 14.4 us there and 15.5 us on the wide
 // kernel, 256 x 4096 15.5 and 16.5; 128 x 14336 24.6 and 18.3, 700 x 2560
 // (asymmetric) 22.6 and 16.5.
 static bool tq_ring_512(int64_t n, int64_t d) { return n * d <= int64_t{1} << 20; }
+static hipError_t device_cu_count(int64_t& cus) {
+    int dev = 0, v = 0;
+    hipError_t err = hipGetDevice(&dev);
+    if (err == hipSuccess) err = hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev);
+    cus = v;
+    return err;
+}
 
 // Grid of the ring kernels: two resident workgroups per CU, R token-tile
 // rows per block rounded down so that every workgroup is resident at once
@@ -2124,16 +2144,11 @@ static int64_t tq_ring_grid(int64_t n, int64_t d, int cus, int64_t& R) {
 
 template <int K, int QM, bool ASYM = false>
 hipError_t launch_tq_ring(const uint16_t* X, int64_t n, int64_t d, const uint16_t* T,
-                          uint8_t* codes, float* s_x, uint32_t* ws, hipStream_t stream,
+                          uint8_t* codes, float* s_x, uint32_t* ws, int64_t cus, hipStream_t stream,
                           float* zmin_x = nullptr) {
-    int dev = 0, cus = 0;
-    hipError_t err = hipGetDevice(&dev);
-    if (err != hipSuccess) return err;
-    err = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-    if (err != hipSuccess) return err;
     int64_t R = 0;
     const int64_t grid = tq_ring_grid<K>(n, d, cus, R);
-    err = launch_fill_zero(ws, ASYM ? 4 * n : n, stream);
+    hipError_t err = launch_fill_zero(ws, ASYM ? 4 * n : n, stream);
     if (err != hipSuccess) return err;
     hipLaunchKernelGGL((tq_ring_kernel<K, false, 7, ASYM>), dim3(static_cast<uint32_t>(grid)),
                        dim3(kTqThreads), 0, stream, X, T, n, d, R, ws, codes, s_x, zmin_x);
@@ -2320,17 +2335,28 @@ static hipError_t launch_tq_qm(const void* X, int x_bf16, int64_t n, int64_t d, 
     }
     amax_ws = reinterpret_cast<uint32_t*>(reinterpret_cast<uint8_t*>(amax_ws) +
                                           tq_twopass_offset(n, d));
+    int64_t cus = 0;
+    if (x_bf16 && t_bf16 && k >= 32) {
+        const hipError_t err = device_cu_count(cus);
+        if (err != hipSuccess) return err;
+    }
     if (x_bf16 && t_bf16 && tq_spans_fit(d, k)) {
         const uint16_t* Xb = static_cast<const uint16_t*>(X);
         const uint16_t* Tb = static_cast<const uint16_t*>(T);
         switch (k) {
-            case 32: return launch_tq_group<32, QM>(Xb, n, d, Tb, codes, s_x, amax_ws, stream);
-            case 64: return launch_tq_group<64, QM>(Xb, n, d, Tb, codes, s_x, amax_ws, stream);
-            case 128: return launch_tq_wide<128, QM>(Xb, n, d, Tb, codes, s_x, amax_ws, stream);
-            case 256: return launch_tq_wide<256, QM>(Xb, n, d, Tb, codes, s_x, amax_ws, stream);
+            case 32: return launch_tq_group<32, QM>(Xb, n, d, Tb, codes, s_x, amax_ws, cus, stream);
+            case 64: return launch_tq_group<64, QM>(Xb, n, d, Tb, codes, s_x, amax_ws, cus, stream);
+            case 128:
+                if (!tq_wide_128(n, d, cus))
+                    return launch_tq_group<128, QM>(Xb, n, d, Tb, codes, s_x, amax_ws, cus, stream);
+                return launch_tq_wide<128, QM>(Xb, n, d, Tb, codes, s_x, amax_ws, cus, stream);
+            case 256:
+                if (!tq_wide_256(n, d, cus))
+                    return launch_tq_group<256, QM>(Xb, n, d, Tb, codes, s_x, amax_ws, cus, stream);
+                return launch_tq_wide<256, QM>(Xb, n, d, Tb, codes, s_x, amax_ws, cus, stream);
             case 512:
                 if (tq_ring_512(n, d)) break;
-                return launch_tq_wide<512, QM>(Xb, n, d, Tb, codes, s_x, amax_ws, stream);
+                return launch_tq_wide<512, QM>(Xb, n, d, Tb, codes, s_x, amax_ws, cus, stream);
             default: break;
         }
     }
@@ -2340,8 +2366,8 @@ static hipError_t launch_tq_qm(const void* X, int x_bf16, int64_t n, int64_t d, 
         switch (k) {
             case 32: return launch_tq_mfma<32, 32, QM>(Xb, n, d, Tb, codes, s_x, amax_ws, stream);
             case 64: return launch_tq_mfma<64, 64, QM>(Xb, n, d, Tb, codes, s_x, amax_ws, stream);
-            case 128: return launch_tq_ring<128, QM>(Xb, n, d, Tb, codes, s_x, amax_ws, stream);
-            case 512: return launch_tq_ring<512, QM>(Xb, n, d, Tb, codes, s_x, amax_ws, stream);
+            case 128: return launch_tq_ring<128, QM>(Xb, n, d, Tb, codes, s_x, amax_ws, cus, stream);
+            case 512: return launch_tq_ring<512, QM>(Xb, n, d, Tb, codes, s_x, amax_ws, cus, stream);
             default: break;
         }
     }
@@ -2406,17 +2432,28 @@ hipError_t launch_transform_quant_asym(const void* X, int x_bf16, int64_t n, int
         if (e != hipSuccess || launched) return e;
     }
     ws = reinterpret_cast<uint32_t*>(reinterpret_cast<uint8_t*>(ws) + tq_twopass_offset(n, d));
+    int64_t cus = 0;
+    if (x_bf16 && t_bf16 && k >= 32) {
+        const hipError_t err = device_cu_count(cus);
+        if (err != hipSuccess) return err;
+    }
     if (x_bf16 && t_bf16 && tq_spans_fit(d, k)) {
         const uint16_t* Xb = static_cast<const uint16_t*>(X);
         const uint16_t* Tb = static_cast<const uint16_t*>(T);
         switch (k) {
-            case 32: return launch_tq_group<32, 7, true>(Xb, n, d, Tb, codes, s_x, ws, stream, zmin_x);
-            case 64: return launch_tq_group<64, 7, true>(Xb, n, d, Tb, codes, s_x, ws, stream, zmin_x);
-            case 128: return launch_tq_wide<128, 7, true>(Xb, n, d, Tb, codes, s_x, ws, stream, zmin_x);
-            case 256: return launch_tq_wide<256, 7, true>(Xb, n, d, Tb, codes, s_x, ws, stream, zmin_x);
+            case 32: return launch_tq_group<32, 7, true>(Xb, n, d, Tb, codes, s_x, ws, cus, stream, zmin_x);
+            case 64: return launch_tq_group<64, 7, true>(Xb, n, d, Tb, codes, s_x, ws, cus, stream, zmin_x);
+            case 128:
+                if (!tq_wide_128(n, d, cus))
+                    return launch_tq_group<128, 7, true>(Xb, n, d, Tb, codes, s_x, ws, cus, stream, zmin_x);
+                return launch_tq_wide<128, 7, true>(Xb, n, d, Tb, codes, s_x, ws, cus, stream, zmin_x);
+            case 256:
+                if (!tq_wide_256(n, d, cus))
+                    return launch_tq_group<256, 7, true>(Xb, n, d, Tb, codes, s_x, ws, cus, stream, zmin_x);
+                return launch_tq_wide<256, 7, true>(Xb, n, d, Tb, codes, s_x, ws, cus, stream, zmin_x);
             case 512:
                 if (tq_ring_512(n, d)) break;
-                return launch_tq_wide<512, 7, true>(Xb, n, d, Tb, codes, s_x, ws, stream, zmin_x);
+                return launch_tq_wide<512, 7, true>(Xb, n, d, Tb, codes, s_x, ws, cus, stream, zmin_x);
             default: break;
         }
     }
@@ -2424,8 +2461,8 @@ hipError_t launch_transform_quant_asym(const void* X, int x_bf16, int64_t n, int
         const uint16_t* Xb = static_cast<const uint16_t*>(X);
         const uint16_t* Tb = static_cast<const uint16_t*>(T);
         switch (k) {
-            case 128: return launch_tq_ring<128, 7, true>(Xb, n, d, Tb, codes, s_x, ws, stream, zmin_x);
-            case 512: return launch_tq_ring<512, 7, true>(Xb, n, d, Tb, codes, s_x, ws, stream, zmin_x);
+            case 128: return launch_tq_ring<128, 7, true>(Xb, n, d, Tb, codes, s_x, ws, cus, stream, zmin_x);
+            case 512: return launch_tq_ring<512, 7, true>(Xb, n, d, Tb, codes, s_x, ws, cus, stream, zmin_x);
             default:
                 return launch_tq_generic_asym(Xb, n, d, Tb, k, codes, s_x, zmin_x, ws, stream);
         }
