@@ -2116,8 +2116,16 @@ static bool tq_wide_256(int64_t n, int64_t d, int64_t cus) {
 // At k = 512 a call of few tiles is all ramp, and the ring kernel's workgroups
 // load half as much of T: 64 x 1024 took 14.4 us there and 15.5 us on the wide
 // kernel, 256 x 4096 15.5 and 16.5; 128 x 14336 24.6 and 18.3, 700 x 2560
-// (asymmetric) 22.6 and 16.5.
-static bool tq_ring_512(int64_t n, int64_t d) { return n * d <= int64_t{1} << 20; }
+// (asymmetric) 22.6 and 16.5.  So it is for few tokens of rows that take more
+// than one round of the wide kernel's workgroups (64 x 98304 50.9 and 56.9, 129
+// 70.1 and 74.6, but 200 86.1 and 84.2), or one round each whose second tile is
+// mostly empty: the ring kernel's tiles are 32 tokens (65 x 65536 39.2 and
+// 43.4, 128 47.3 and 44.5).
+static bool tq_ring_512(int64_t n, int64_t d, int64_t cus) {
+    const int64_t wgs = d / kTwRows;
+    if (n * d <= int64_t{1} << 20) return true;
+    return wgs > cus ? n < 160 : 2 * wgs > cus && n > kTwTT && n <= 96;
+}
 static hipError_t device_cu_count(int64_t& cus) {
     int dev = 0, v = 0;
     hipError_t err = hipGetDevice(&dev);
@@ -2355,7 +2363,7 @@ static hipError_t launch_tq_qm(const void* X, int x_bf16, int64_t n, int64_t d, 
                     return launch_tq_group<256, QM>(Xb, n, d, Tb, codes, s_x, amax_ws, cus, stream);
                 return launch_tq_wide<256, QM>(Xb, n, d, Tb, codes, s_x, amax_ws, cus, stream);
             case 512:
-                if (tq_ring_512(n, d)) break;
+                if (tq_ring_512(n, d, cus)) break;
                 return launch_tq_wide<512, QM>(Xb, n, d, Tb, codes, s_x, amax_ws, cus, stream);
             default: break;
         }
@@ -2452,7 +2460,7 @@ hipError_t launch_transform_quant_asym(const void* X, int x_bf16, int64_t n, int
                     return launch_tq_group<256, 7, true>(Xb, n, d, Tb, codes, s_x, ws, cus, stream, zmin_x);
                 return launch_tq_wide<256, 7, true>(Xb, n, d, Tb, codes, s_x, ws, cus, stream, zmin_x);
             case 512:
-                if (tq_ring_512(n, d)) break;
+                if (tq_ring_512(n, d, cus)) break;
                 return launch_tq_wide<512, 7, true>(Xb, n, d, Tb, codes, s_x, ws, cus, stream, zmin_x);
             default: break;
         }
