@@ -34,13 +34,15 @@ constexpr int kCovTK = 32;        // tokens per LDS slab
 
 // Decode a linear index over the upper triangle of a T x T tile grid.
 __device__ __forceinline__ void tri_decode(int64_t idx, int64_t T, int64_t& I, int64_t& J) {
-    int64_t i = 0;
-    while (idx >= T - i) {
-        idx -= T - i;
-        ++i;
-    }
+    // row i starts at i (2 T + 1 - i) / 2: the root of that quadratic, put right
+    // where rounding moved it (walking the rows took a microsecond at T = 64)
+    const double b = static_cast<double>(2 * T + 1);
+    int64_t i = static_cast<int64_t>((b - __builtin_sqrt(b * b - 8.0 * static_cast<double>(idx))) * 0.5);
+    auto start = [&](int64_t r) { return r * (2 * T + 1 - r) / 2; };
+    while (start(i) > idx) --i;
+    while (start(i + 1) <= idx) ++i;
     I = i;
-    J = i + idx;
+    J = i + (idx - start(i));
 }
 
 struct CovTile {
@@ -221,14 +223,14 @@ __global__ __launch_bounds__(kCovThreads) void cov_mfma_kernel(const uint16_t* _
 //
 // The operands need no LDS: a fragment is 4 token rows of 16 channels, read
 // from global memory.  With VEC a lane reads NT consecutive channels at once
-// and fragment a is channels a, NT + a, 2 NT + a, ... of the tile (the vector
-// memory path takes about as long for a 4-byte load as for a 16-byte one, and
-// bounds the small tiles); without it, channels 16 a ... 16 a + 15.  Small
-// problems are bound by latency, so the launcher takes the largest tile that
-// still gives half the CUs one: 512 tokens of 8 blocks of 32 channels took 66
-// us as 8 workgroups of 64 x 64 vector-ALU tiles walking all tokens and take
-// under 9 us; 2048 x 512, whole matrix, 368 us and 27 us; 8192 x 1024 1527 us
-// and 275 us.
+// and fragment a is channels a, NT + a, ... of the tile (the vector memory path
+// takes about as long for a 4-byte load as for a longer one, and bounds the
+// small tiles); without it, channels 16 a ... 16 a + 15.  Bound by the fp64 MFMA
+// rate at many tokens, at few by the latency of a tile (load, reduce, update
+// acc) and how many tiles a CU holds at once, so tiles are small and registers
+// are kept few.  Against 64 x 64 vector-ALU tiles walking all tokens: 512
+// tokens of 8 blocks of 32 channels 66 -> 6.4 us; 2048 x 512, whole matrix, 368
+// -> 22 us; 8192 x 1024 1527 -> 215 us; 1 x 2048 18.6 -> 14.9.
 typedef double f64x4 __attribute__((ext_vector_type(4)));
 constexpr int kCovFWaves = 8;
 constexpr int kCovFThreads = kCovFWaves * kWave;
@@ -249,38 +251,49 @@ __device__ __forceinline__ void cov_load_vec(const uint16_t* p, float (&v)[NT]) 
     for (int a = 0; a < NT; ++a) v[a] = bf16_bits_to_f32(x[a]);
 }
 
-template <typename XT, int NT, bool VEC>
-__global__ __launch_bounds__(kCovFThreads) void cov_f64_kernel(const XT* __restrict__ X, int64_t n,
+template <typename XT, int NT, int UN, bool VEC, typename Off = uint32_t>
+__global__ __launch_bounds__(kCovFThreads, UN == 4 ? 6 : 2) void cov_f64_kernel(const XT* __restrict__ X, int64_t n,
                                                                int64_t d, int mode, int64_t k,
                                                                float* __restrict__ acc) {
     constexpr int TILE = 16 * NT;
-    constexpr int UN = NT == 4 ? 4 : 8;             // 4-token groups in flight per wave
     constexpr int kStep = UN * kCovFWaves;          // groups per round of the 8 waves
-    __shared__ f64x4 red[kCovFWaves][NT * kWave];
+    constexpr int kRow = NT * 4 * kWave;            // values of one row of fragments
+    constexpr int PER = (TILE * TILE + kCovFThreads - 1) / kCovFThreads;   // tile elements per thread
+    __shared__ double red[kCovFWaves][kRow];
+    __shared__ double sums[TILE][TILE];              // element (r, c) at [r][c ^ r]
     const CovTile ct = cov_tile(blockIdx.x, TILE, d, mode, k);
     const bool diag = ct.I0 == ct.J0;
     const int tid = threadIdx.x;
-    const int lane = tid & (kWave - 1), wave = tid / kWave;
+    const int lane = tid & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(tid / kWave);
     const int l16 = lane & 15, q4 = lane >> 4;
     // channel of fragment a, lane or row i, inside the tile
     auto chan = [](int a, int i) { return VEC ? NT * i + a : 16 * a + i; };
-    // channels past the matrix read a valid one (their results are not stored)
-    int64_t ca[NT], cb[NT];
+    // A lane's bytes from the first element of a group of 4 token rows (a
+    // wave-uniform address, so that a load costs no address registers of its
+    // own): its row, and its channels of each fragment.  Channels past the
+    // matrix read a valid one (their results are not stored).
+    const Off row = static_cast<Off>(q4 * d * static_cast<int64_t>(sizeof(XT)));
+    Off ca[NT], cb[NT];
 #pragma unroll
     for (int a = 0; a < NT; ++a) {
         const int64_t ci = ct.I0 + chan(a, l16), cj = ct.J0 + chan(a, l16);
-        ca[a] = ct.colbase + (ci < ct.dim ? ci : 0);
-        cb[a] = ct.colbase + (cj < ct.dim ? cj : 0);
+        ca[a] = static_cast<Off>((ci < ct.dim ? ci : 0) * static_cast<int64_t>(sizeof(XT)));
+        cb[a] = static_cast<Off>((cj < ct.dim ? cj : 0) * static_cast<int64_t>(sizeof(XT)));
     }
-    auto load = [&](const XT* row, float (&xa)[NT], float (&xb)[NT]) {
+    X += ct.colbase;
+    acc += ct.base;
+    auto load = [&](const XT* group, Off r, float (&xa)[NT], float (&xb)[NT]) {
+        auto elem = [&](Off o) {
+            return reinterpret_cast<const XT*>(reinterpret_cast<const uint8_t*>(group) + (r + o));
+        };
         if constexpr (VEC) {
-            cov_load_vec<NT>(row + ca[0], xa);
-            cov_load_vec<NT>(row + cb[0], xb);
+            cov_load_vec<NT>(elem(ca[0]), xa);
+            cov_load_vec<NT>(elem(cb[0]), xb);
         } else {
 #pragma unroll
             for (int a = 0; a < NT; ++a) {
-                xa[a] = load_as_f32(row, ca[a]);
-                xb[a] = load_as_f32(row, cb[a]);
+                xa[a] = load_as_f32(elem(ca[a]), 0);
+                xb[a] = load_as_f32(elem(cb[a]), 0);
             }
         }
     };
@@ -291,71 +304,110 @@ __global__ __launch_bounds__(kCovFThreads) void cov_f64_kernel(const XT* __restr
         for (int a = 0; a < NT; ++a)
 #pragma unroll
             for (int b = 0; b < NT; ++b) part[a][b] = f64x4{0.0, 0.0, 0.0, 0.0};
-        auto products = [&](const float (&xa)[UN][NT], const float (&xb)[UN][NT]) {
+        auto products = [&](const float (&xa)[NT], const float (&xb)[NT]) {
 #pragma unroll
-            for (int u = 0; u < UN; ++u)
+            for (int a = 0; a < NT; ++a)
 #pragma unroll
-                for (int a = 0; a < NT; ++a)
-#pragma unroll
-                    for (int b = 0; b < NT; ++b)
-                        part[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(
-                            static_cast<double>(xa[u][a]), static_cast<double>(xb[u][b]), part[a][b], 0, 0, 0);
+                for (int b = 0; b < NT; ++b)
+                    part[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(
+                        static_cast<double>(xa[a]), static_cast<double>(xb[b]), part[a][b], 0, 0, 0);
         };
-        int64_t t = f0 + 4 * wave + q4;              // this lane's token of the wave's first group
+        int64_t t = f0 + 4 * wave;                   // the wave's first group
         const int64_t full = f0 + (f1 - f0) / (4 * kStep) * (4 * kStep);   // whole rounds end here
         for (; t < full; t += 4 * kStep) {
             float xa[UN][NT], xb[UN][NT];
-            const XT* row = X + t * d;
+            Off r = row;
+            asm volatile("" : "+v"(r));     // or the loop steps an address in registers for each of its loads
 #pragma unroll
-            for (int u = 0; u < UN; ++u) load(row + u * (4 * kCovFWaves) * d, xa[u], xb[u]);
-            products(xa, xb);
+            for (int u = 0; u < UN; ++u) load(X + (t + u * (4 * kCovFWaves)) * d, r, xa[u], xb[u]);
+#pragma unroll
+            for (int u = 0; u < UN; ++u) products(xa[u], xb[u]);
         }
-        if (full < f1) {
-            // the last, ragged round: tokens past the end are zeros
+        if (t < f1) {
+            // the last, ragged round, for waves that have a token in it: tokens
+            // past the end are zeros
             float xa[UN][NT], xb[UN][NT];
 #pragma unroll
             for (int u = 0; u < UN; ++u) {
                 const int64_t tu = t + u * (4 * kCovFWaves);
-                const bool live = tu < f1;
-                load(X + (live ? tu : f0) * d, xa[u], xb[u]);
+                const bool live = tu + q4 < f1;
+                load(X + (tu < f1 ? tu : f0) * d, live ? row : 0, xa[u], xb[u]);
 #pragma unroll
                 for (int a = 0; a < NT; ++a) {
                     xa[u][a] = live ? xa[u][a] : 0.0f;
                     xb[u][a] = live ? xb[u][a] : 0.0f;
                 }
             }
-            products(xa, xb);
+#pragma unroll
+            for (int u = 0; u < UN; ++u)
+                if (t + u * (4 * kCovFWaves) < f1) products(xa[u], xb[u]);
         }
-        // owner flush: acc += sums (and the transpose off the diagonal), one
-        // row of fragments at a time; a lane's four values are rows q4, q4 +
-        // 4, q4 + 8, q4 + 12 of column l16
+        // owner flush: acc += sums (and the transpose off the diagonal).  The
+        // waves' sums of one row of fragments at a time meet in LDS (a lane's
+        // four values are rows q4, q4 + 4, q4 + 8, q4 + 12 of column l16), and
+        // whole rows of the tile go to acc, whose old values are requested
+        // before the sums are formed.  (Updating acc value by value from the
+        // fragments, a chain of dependent 4-byte reads and writes, bound calls of
+        // few tokens: with 64 x 64 tiles 1 x 2048 took 44 us, 64 x 14336 in blocks
+        // of 128 27 us, now 15 and 15.)
+        float own[PER], mir[PER];
+        int first = tid;
+        asm volatile("" : "+v"(first));     // or the addresses below are kept in registers all through
+        auto at = [&](int64_t r0, int64_t c0, int i) -> float* {
+            const int e = i * kCovFThreads + first;
+            const int64_t r = r0 + e / TILE, c = c0 + e % TILE;
+            if (e >= TILE * TILE || r >= ct.dim || c >= ct.dim) return nullptr;
+            return acc + r * ct.dim + c;
+        };
 #pragma unroll
-        for (int a = 0; a < NT; ++a) {
-            __syncthreads();
+        for (int i = 0; i < PER; ++i) {
+            const float* p = at(ct.I0, ct.J0, i);
+            own[i] = p ? *p : 0.0f;
+            const float* m = diag ? nullptr : at(ct.J0, ct.I0, i);
+            mir[i] = m ? *m : 0.0f;
+        }
+        const int waves = f1 - f0 < 4 * kCovFWaves ? static_cast<int>(f1 - f0 + 3) / 4 : kCovFWaves;   // with a token
+        auto put = [&](int a, int slot) {
+            if (wave >= waves) return;
 #pragma unroll
-            for (int b = 0; b < NT; ++b) red[wave][b * kWave + lane] = part[a][b];
-            __syncthreads();
-            if (tid < NT * kWave) {
-                f64x4 v = red[0][tid];
+            for (int b = 0; b < NT; ++b)
 #pragma unroll
-                for (int w = 1; w < kCovFWaves; ++w) {
-                    const f64x4 p = red[w][tid];
+                for (int r = 0; r < 4; ++r) red[slot + wave][(4 * b + r) * kWave + lane] = part[a][b][r];
+        };
+        auto sum = [&](int a, int slot) {
 #pragma unroll
-                    for (int r = 0; r < 4; ++r) v[r] += p[r];
-                }
-                const int64_t gj = ct.J0 + chan(wave, l16);     // tid / 64: the column fragment
+            for (int e = tid; e < kRow; e += kCovFThreads) {
+                double v = red[slot][e];
 #pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const int64_t gi = ct.I0 + chan(a, 4 * r + q4);
-                    if (gi >= ct.dim || gj >= ct.dim) continue;
-                    float* ptr = acc + ct.base + gi * ct.dim + gj;
-                    *ptr = static_cast<float>(*ptr + v[r]);
-                    if (!diag) {
-                        float* m = acc + ct.base + gj * ct.dim + gi;
-                        *m = static_cast<float>(*m + v[r]);
-                    }
-                }
+                for (int w = 1; w < kCovFWaves; ++w)
+                    if (w < waves) v += red[slot + w][e];
+                const int i = chan(a, 4 * ((e / kWave) & 3) + q4);   // e is of this thread's lane
+                sums[i][chan(e / (4 * kWave), l16) ^ i] = v;
             }
+        };
+        __syncthreads();
+        if (NT == 2 && waves <= kCovFWaves / 2) {                // room for both rows at once
+            put(0, 0);
+            put(NT - 1, kCovFWaves / 2);
+            __syncthreads();
+            sum(0, 0);
+            sum(NT - 1, kCovFWaves / 2);
+        } else {
+#pragma unroll
+            for (int a = 0; a < NT; ++a) {
+                if (a > 0) __syncthreads();
+                put(a, 0);
+                __syncthreads();
+                sum(a, 0);
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < PER; ++i) {
+            const int e = i * kCovFThreads + first;
+            const int r = e / TILE, c = e % TILE;
+            if (float* p = at(ct.I0, ct.J0, i)) *p = static_cast<float>(own[i] + sums[r][c ^ r]);
+            if (float* m = diag ? nullptr : at(ct.J0, ct.I0, i)) *m = static_cast<float>(mir[i] + sums[c][c ^ r]);
         }
     }
 }
@@ -925,16 +977,16 @@ static int64_t cov_grid(int tile, int64_t d, int mode, int64_t k) {
     return (d / k) * (T * (T + 1) / 2);
 }
 
-template <typename XT, int NT>
+template <typename XT, int NT, int UN>
 static hipError_t launch_cov_f64_tile(const XT* X, int64_t n, int64_t d, int mode, int64_t k,
                                       float* acc, hipStream_t stream) {
     const dim3 g(static_cast<uint32_t>(cov_grid(16 * NT, d, mode, k))), blk(kCovFThreads);
     // NT channels at once where every row and matrix starts on a whole vector
     const int64_t dim = mode == CAT_COV_FULL ? d : k;
     if (NT > 1 && d % NT == 0 && dim % NT == 0)
-        hipLaunchKernelGGL((cov_f64_kernel<XT, NT, (NT > 1)>), g, blk, 0, stream, X, n, d, mode, k, acc);
+        hipLaunchKernelGGL((cov_f64_kernel<XT, NT, UN, (NT > 1)>), g, blk, 0, stream, X, n, d, mode, k, acc);
     else
-        hipLaunchKernelGGL((cov_f64_kernel<XT, NT, false>), g, blk, 0, stream, X, n, d, mode, k, acc);
+        hipLaunchKernelGGL((cov_f64_kernel<XT, NT, UN, false>), g, blk, 0, stream, X, n, d, mode, k, acc);
     return hipGetLastError();
 }
 
@@ -944,13 +996,25 @@ static hipError_t launch_cov_f64(const XT* X, int64_t n, int64_t d, int mode, in
     int cus = 0;
     const hipError_t err = device_cus(cus);
     if (err != hipSuccess) return err;
-    // the largest tile (fewest reads per product) that gives half the CUs one
+    if (d >= int64_t{1} << 28) {     // four rows exceed 32-bit offsets
+        hipLaunchKernelGGL((cov_f64_kernel<XT, 1, 8, false, uint64_t>),
+                           dim3(static_cast<uint32_t>(cov_grid(16, d, mode, k))), dim3(kCovFThreads), 0,
+                           stream, X, n, d, mode, k, acc);
+        return hipGetLastError();
+    }
+    // 32 x 32 tiles where half the CUs get one (fewer reads per product), else
+    // 16 x 16.  (64 x 64 tiles, whose 200 registers leave two waves per SIMD,
+    // took 60% longer: 1024 x 14336, blocks of 128, 87 us and 52; 2048 x 2048,
+    // whole matrix, 228 and 159.)
     const int64_t dim = mode == CAT_COV_FULL ? d : k;
-    if (2 * cov_grid(64, d, mode, k) >= cus && dim > 32)
-        return launch_cov_f64_tile<XT, 4>(X, n, d, mode, k, acc, stream);
-    if (2 * cov_grid(32, d, mode, k) >= cus && dim > 16)
-        return launch_cov_f64_tile<XT, 2>(X, n, d, mode, k, acc, stream);
-    return launch_cov_f64_tile<XT, 1>(X, n, d, mode, k, acc, stream);
+    if (2 * cov_grid(32, d, mode, k) >= cus && dim > 16) {
+        // four token groups in flight per wave leave room for more workgroups
+        // per CU, which is what few tokens need: 64 x 2047 30 us against 37,
+        // but 2048 x 2047 192 against 178
+        if (n <= 4 * 4 * kCovFWaves) return launch_cov_f64_tile<XT, 2, 4>(X, n, d, mode, k, acc, stream);
+        return launch_cov_f64_tile<XT, 2, 8>(X, n, d, mode, k, acc, stream);
+    }
+    return launch_cov_f64_tile<XT, 1, 8>(X, n, d, mode, k, acc, stream);
 }
 
 hipError_t launch_cov_accumulate(const void* X, int x_bf16, int64_t n, int64_t d, int mode,

@@ -17,12 +17,14 @@ pytestmark = pytest.mark.gpu
     ("full", 5, 1, 3, "f32"),            # one 16 x 16 tile, mostly outside the matrix
     ("full", 100, 1, 4097, "f32"),       # 16 x 16 tiles, a second flush of one token
     ("full", 1040, 1, 37, "f32"),        # 32 x 32 tiles, ragged last one
-    ("full", 1604, 1, 50, "f32"),        # 64 x 64 tiles, ragged last one
+    ("full", 1604, 1, 50, "f32"),        # the same, ragged by a part of a fragment
     ("block", 40, 8, 130, "f32"),        # blocks smaller than a tile
     ("block", 256, 32, 512, "f32"),      # three 16 x 16 tiles per block
-    ("block", 16384, 64, 9, "f32"),      # one 64 x 64 tile per block
+    ("block", 16384, 64, 9, "f32"),      # three 32 x 32 tiles per block
     ("block", 8192, 32, 70, "f32"),      # one 32 x 32 tile per block
     ("block", 96, 16, 200, "bf16"),
+    ("block", 8224, 32, 70, "bf16"),     # 32 x 32 tiles, two channels at once
+    ("block", 8224, 32, 300, "bf16"),
 ])
 def test_second_moment_fp64_path(mode, d, k, n, dtype):
     torch = torch_mod()
@@ -42,6 +44,29 @@ def test_second_moment_fp64_path(mode, d, k, n, dtype):
     # fp64 sums, rounded to fp32 once per 4096 tokens
     flushes = -(-n // 4096)
     assert np.all(np.abs(got - ref) <= flushes * 2.0 ** -24 * mag * 1.001)
+
+
+# On a 256-CU device full matrices of 481 channels and more run 32 x 32 tiles, up
+# to 128 tokens with four groups of 4 in flight per wave and beyond with eight;
+# an odd width reads channels one by one.  The accumulator starts with values.
+@pytest.mark.parametrize("dtype,d", [("f32", 480), ("f32", 512), ("f32", 560), ("f32", 561), ("f32", 1041),
+                                     ("bf16", 561), ("bf16", 1041)])
+@pytest.mark.parametrize("n", [1, 15, 17, 127, 129, 259])
+def test_second_moment_fp64_path_accumulates(dtype, d, n):
+    torch = torch_mod()
+    say(f"cov full d={d} n={n} {dtype}, non-zero start")
+    rng = np.random.default_rng(d + n)
+    X = o.round_storage(rng.standard_normal((n, d)) * np.exp(rng.standard_normal(d)), dtype)
+    start = rng.standard_normal((d, d)).astype(np.float32)
+    start = start + start.T
+    acc = dev(start, "f32")
+    cat.cat_cov_accumulate(dev(X, dtype), acc, B.CAT_COV_FULL, 1)
+    got = host(acc).astype(np.float64)
+    X = X.astype(np.float64)
+    ref = start.astype(np.float64) + X.T @ X
+    # one rounding of the fp64 sum to fp32
+    assert np.all(np.abs(got - ref) <= 2.0 ** -24 * 1.001 * np.abs(ref) + 2.0 ** -45 * (np.abs(X).T @ np.abs(X)))
+    assert np.array_equal(got, got.T)
 
 
 @pytest.mark.parametrize("x_dtype,t_dtype,d,k,n,bits", [
