@@ -261,7 +261,19 @@ __global__ __launch_bounds__(kCovFThreads, UN == 4 ? 6 : 2) void cov_f64_kernel(
     constexpr int PER = (TILE * TILE + kCovFThreads - 1) / kCovFThreads;   // tile elements per thread
     __shared__ double red[kCovFWaves][kRow];
     __shared__ double sums[TILE][TILE];              // element (r, c) at [r][c ^ r]
-    const CovTile ct = cov_tile(blockIdx.x, TILE, d, mode, k);
+    // blocks of less than 16 channels: a tile is the 16 channels of several, of
+    // which only the blocks are stored (1 x 1 blocks, 2048 x 4096, a workgroup
+    // each took 84 us)
+    const bool packed = NT == 1 && mode == CAT_COV_BLOCK_DIAG && k < TILE;
+    CovTile ct;
+    if (packed) {
+        ct.colbase = blockIdx.x * int64_t{TILE};
+        ct.dim = d - ct.colbase < TILE ? d - ct.colbase : TILE;
+        ct.I0 = ct.J0 = 0;
+        ct.base = ct.colbase * k;
+    } else {
+        ct = cov_tile(blockIdx.x, TILE, d, mode, k);
+    }
     const bool diag = ct.I0 == ct.J0;
     const int tid = threadIdx.x;
     const int lane = tid & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(tid / kWave);
@@ -357,6 +369,7 @@ __global__ __launch_bounds__(kCovFThreads, UN == 4 ? 6 : 2) void cov_f64_kernel(
             const int e = i * kCovFThreads + first;
             const int64_t r = r0 + e / TILE, c = c0 + e % TILE;
             if (e >= TILE * TILE || r >= ct.dim || c >= ct.dim) return nullptr;
+            if (packed) return (r ^ c) < k ? acc + r * k + (c & (k - 1)) : nullptr;
             return acc + r * ct.dim + c;
         };
 #pragma unroll
@@ -973,6 +986,7 @@ static int64_t cov_grid(int tile, int64_t d, int mode, int64_t k) {
         const int64_t T = (d + tile - 1) / tile;
         return T * (T + 1) / 2;
     }
+    if (k < 16 && tile == 16) return (d + 15) / 16;   // several blocks to a tile
     const int64_t T = (k + tile - 1) / tile;
     return (d / k) * (T * (T + 1) / 2);
 }

@@ -23,6 +23,11 @@ pytestmark = pytest.mark.gpu
     ("block", 16384, 64, 9, "f32"),      # three 32 x 32 tiles per block
     ("block", 8192, 32, 70, "f32"),      # one 32 x 32 tile per block
     ("block", 96, 16, 200, "bf16"),
+    ("block", 17, 1, 5, "f32"),          # several blocks to a tile, a ragged last one
+    ("block", 18, 2, 300, "f32"),
+    ("block", 148, 4, 33, "bf16"),
+    ("block", 24, 8, 4100, "f32"),       # and a second flush
+    ("block", 4096, 1, 70, "bf16"),
     ("block", 8224, 32, 70, "bf16"),     # 32 x 32 tiles, two channels at once
     ("block", 8224, 32, 300, "bf16"),
 ])
