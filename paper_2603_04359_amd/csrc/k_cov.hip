@@ -254,7 +254,7 @@ __device__ __forceinline__ void cov_load_vec(const uint16_t* p, float (&v)[NT]) 
 template <typename XT, int NT, int UN, bool VEC, typename Off = uint32_t>
 __global__ __launch_bounds__(kCovFThreads, UN == 4 ? 6 : 2) void cov_f64_kernel(const XT* __restrict__ X, int64_t n,
                                                                int64_t d, int mode, int64_t k,
-                                                               float* __restrict__ acc) {
+                                                               float* __restrict__ acc, int64_t tile0) {
     constexpr int TILE = 16 * NT;
     constexpr int kStep = UN * kCovFWaves;          // groups per round of the 8 waves
     constexpr int kRow = NT * 4 * kWave;            // values of one row of fragments
@@ -265,14 +265,15 @@ __global__ __launch_bounds__(kCovFThreads, UN == 4 ? 6 : 2) void cov_f64_kernel(
     // which only the blocks are stored (1 x 1 blocks, 2048 x 4096, a workgroup
     // each took 84 us)
     const bool packed = NT == 1 && mode == CAT_COV_BLOCK_DIAG && k < TILE;
+    const int64_t work = tile0 + blockIdx.x;
     CovTile ct;
     if (packed) {
-        ct.colbase = blockIdx.x * int64_t{TILE};
+        ct.colbase = work * TILE;
         ct.dim = d - ct.colbase < TILE ? d - ct.colbase : TILE;
         ct.I0 = ct.J0 = 0;
         ct.base = ct.colbase * k;
     } else {
-        ct = cov_tile(blockIdx.x, TILE, d, mode, k);
+        ct = cov_tile(work, TILE, d, mode, k);
     }
     const bool diag = ct.I0 == ct.J0;
     const int tid = threadIdx.x;
@@ -991,17 +992,31 @@ static int64_t cov_grid(int tile, int64_t d, int mode, int64_t k) {
     return (d / k) * (T * (T + 1) / 2);
 }
 
+// A launch covers fewer than 2^32 threads: more tiles than this take several.
+constexpr int64_t kCovFMaxTiles = int64_t{1} << 22;
+
+template <typename XT, int NT, int UN, bool VEC, typename Off = uint32_t>
+static hipError_t launch_cov_f64_kernel(const XT* X, int64_t n, int64_t d, int mode, int64_t k,
+                                        float* acc, hipStream_t stream) {
+    const int64_t tiles = cov_grid(16 * NT, d, mode, k);
+    for (int64_t t = 0; t < tiles; t += kCovFMaxTiles) {
+        const int64_t g = tiles - t < kCovFMaxTiles ? tiles - t : kCovFMaxTiles;
+        hipLaunchKernelGGL((cov_f64_kernel<XT, NT, UN, VEC, Off>), dim3(static_cast<uint32_t>(g)),
+                           dim3(kCovFThreads), 0, stream, X, n, d, mode, k, acc, t);
+        const hipError_t err = hipGetLastError();
+        if (err != hipSuccess) return err;
+    }
+    return hipSuccess;
+}
+
 template <typename XT, int NT, int UN>
 static hipError_t launch_cov_f64_tile(const XT* X, int64_t n, int64_t d, int mode, int64_t k,
                                       float* acc, hipStream_t stream) {
-    const dim3 g(static_cast<uint32_t>(cov_grid(16 * NT, d, mode, k))), blk(kCovFThreads);
     // NT channels at once where every row and matrix starts on a whole vector
     const int64_t dim = mode == CAT_COV_FULL ? d : k;
     if (NT > 1 && d % NT == 0 && dim % NT == 0)
-        hipLaunchKernelGGL((cov_f64_kernel<XT, NT, UN, (NT > 1)>), g, blk, 0, stream, X, n, d, mode, k, acc);
-    else
-        hipLaunchKernelGGL((cov_f64_kernel<XT, NT, UN, false>), g, blk, 0, stream, X, n, d, mode, k, acc);
-    return hipGetLastError();
+        return launch_cov_f64_kernel<XT, NT, UN, (NT > 1)>(X, n, d, mode, k, acc, stream);
+    return launch_cov_f64_kernel<XT, NT, UN, false>(X, n, d, mode, k, acc, stream);
 }
 
 template <typename XT>
@@ -1010,12 +1025,8 @@ static hipError_t launch_cov_f64(const XT* X, int64_t n, int64_t d, int mode, in
     int cus = 0;
     const hipError_t err = device_cus(cus);
     if (err != hipSuccess) return err;
-    if (d >= int64_t{1} << 28) {     // four rows exceed 32-bit offsets
-        hipLaunchKernelGGL((cov_f64_kernel<XT, 1, 8, false, uint64_t>),
-                           dim3(static_cast<uint32_t>(cov_grid(16, d, mode, k))), dim3(kCovFThreads), 0,
-                           stream, X, n, d, mode, k, acc);
-        return hipGetLastError();
-    }
+    if (d >= int64_t{1} << 28)       // four rows exceed 32-bit offsets
+        return launch_cov_f64_kernel<XT, 1, 8, false, uint64_t>(X, n, d, mode, k, acc, stream);
     // 32 x 32 tiles where half the CUs get one (fewer reads per product), else
     // 16 x 16.  (64 x 64 tiles, whose 200 registers leave two waves per SIMD,
     // took 60% longer: 1024 x 14336, blocks of 128, 87 us and 52; 2048 x 2048,

@@ -350,18 +350,28 @@ __global__ __launch_bounds__(kTrThreads) void tq_rows_kernel(
 
 static bool tq_rows_fits(int64_t d, int64_t k) { return k >= 16 && d <= kTrMaxD; }
 
+// A launch covers fewer than 2^32 threads: more tokens than this take several.
+constexpr int64_t kTrMaxTokens = int64_t{kTrTokens} << 21;
+
 template <int QM, bool ASYM, typename XT, typename TT>
 static hipError_t launch_tq_rows(const XT* X, int64_t n, int64_t d, const TT* T, int64_t k,
                                  uint8_t* codes, float* s_x, float* zmin_x, hipStream_t stream) {
-    const dim3 grid(static_cast<uint32_t>((n + kTrTokens - 1) / kTrTokens)), block(kTrThreads);
-    // tiles per wave held in registers
-    if (d <= 16 * kTrWaves * 4)
-        hipLaunchKernelGGL((tq_rows_kernel<XT, TT, QM, ASYM, 4>), grid, block, 0, stream, X, T, n, d,
-                           static_cast<int>(k), codes, s_x, zmin_x);
-    else
-        hipLaunchKernelGGL((tq_rows_kernel<XT, TT, QM, ASYM, kTrMaxTiles>), grid, block, 0, stream, X,
-                           T, n, d, static_cast<int>(k), codes, s_x, zmin_x);
-    return hipGetLastError();
+    for (int64_t t = 0; t < n; t += kTrMaxTokens) {
+        const int64_t m = n - t < kTrMaxTokens ? n - t : kTrMaxTokens;
+        const dim3 grid(static_cast<uint32_t>((m + kTrTokens - 1) / kTrTokens)), block(kTrThreads);
+        uint8_t* const c = codes + t * (QM == 7 ? d / 2 : d);
+        float* const zmin = ASYM ? zmin_x + t : nullptr;
+        // tiles per wave held in registers
+        if (d <= 16 * kTrWaves * 4)
+            hipLaunchKernelGGL((tq_rows_kernel<XT, TT, QM, ASYM, 4>), grid, block, 0, stream, X + t * d,
+                               T, m, d, static_cast<int>(k), c, s_x + t, zmin);
+        else
+            hipLaunchKernelGGL((tq_rows_kernel<XT, TT, QM, ASYM, kTrMaxTiles>), grid, block, 0, stream,
+                               X + t * d, T, m, d, static_cast<int>(k), c, s_x + t, zmin);
+        const hipError_t err = hipGetLastError();
+        if (err != hipSuccess) return err;
+    }
+    return hipSuccess;
 }
 
 // --------------------------------------------------------------- MFMA path
