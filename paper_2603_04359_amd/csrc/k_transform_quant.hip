@@ -348,7 +348,16 @@ __global__ __launch_bounds__(kTrThreads) void tq_rows_kernel(
     }
 }
 
-static bool tq_rows_fits(int64_t d, int64_t k) { return k >= 16 && d <= kTrMaxD; }
+// One workgroup reads all of T for up to 16 tokens, so one or two tokens with
+// the largest T stay on the two-pass kernels, which spread over the chip: at
+// 4096 channels, k = 512, fp32 X and T, one token takes 290 us there and 312
+// here, bf16 X 292 and 332, two 314 and 330, three 337 and 329; asymmetric (two
+// atomics per pair) one 315 and 334, two 361 and 332; one token at 3584
+// channels 286 and 273, at k = 256 159 and 155.
+template <bool ASYM>
+static bool tq_rows_fits(int64_t n, int64_t d, int64_t k) {
+    return k >= 16 && d <= kTrMaxD && (n > (ASYM ? 1 : 2) || d * k < int64_t{1} << 21);
+}
 
 // A launch covers fewer than 2^32 threads: more tokens than this take several.
 constexpr int64_t kTrMaxTokens = int64_t{kTrTokens} << 21;
@@ -2324,7 +2333,7 @@ hipError_t launch_tq_fused(const uint16_t* X, int64_t n, int64_t d, const uint16
 template <int QM, typename XT, typename TT>
 hipError_t launch_tq_generic(const XT* X, int64_t n, int64_t d, const TT* T, int64_t k,
                              uint8_t* codes, float* s_x, uint32_t* ws, hipStream_t stream) {
-    if (tq_rows_fits(d, k))
+    if (tq_rows_fits<false>(n, d, k))
         return launch_tq_rows<QM, false>(X, n, d, T, k, codes, s_x, nullptr, stream);
     hipError_t err = launch_fill_zero(ws, n, stream);
     if (err != hipSuccess) return err;
@@ -2419,7 +2428,7 @@ template <typename XT, typename TT>
 static hipError_t launch_tq_generic_asym(const XT* X, int64_t n, int64_t d, const TT* T,
                                          int64_t k, uint8_t* codes, float* s_x, float* zmin_x,
                                          uint32_t* ws, hipStream_t stream) {
-    if (tq_rows_fits(d, k))
+    if (tq_rows_fits<true>(n, d, k))
         return launch_tq_rows<7, true>(X, n, d, T, k, codes, s_x, zmin_x, stream);
     hipError_t err = launch_fill_zero(ws, 4 * n, stream);
     if (err != hipSuccess) return err;

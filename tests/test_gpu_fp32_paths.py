@@ -80,6 +80,8 @@ def test_second_moment_fp64_path_accumulates(dtype, d, n):
     ("f32", "bf16", 1024, 64, 33, 6),        # four tiles per wave, one token in the last workgroup
     ("bf16", "f32", 1040, 16, 17, 4),        # more than four, ragged over the waves
     ("f32", "f32", 4096, 512, 18, 4),        # the widest row and block
+    ("bf16", "f32", 4096, 512, 2, 4),        # one zero token and another: the two-pass kernels
+    ("f32", "bf16", 4096, 512, 3, 8),
     ("f32", "f32", 4112, 16, 5, 4),          # wider: the two-pass kernels
     ("bf16", "bf16", 4096, 16, 40, 8),
 ])
