@@ -138,14 +138,15 @@ __global__ __launch_bounds__(kTqThreads) void tq_generic_amax_kernel(
     const XT* __restrict__ X, const TT* __restrict__ T, int64_t n, int64_t d, int64_t k,
     uint32_t* __restrict__ amax_ws) {
     const int64_t pairs = d / 2;
-    const int64_t u = static_cast<int64_t>(blockIdx.x) * kTqThreads + threadIdx.x;
-    if (u >= n * pairs) return;
-    const int64_t t = u / pairs;
-    const int64_t c = 2 * (u - t * pairs);
-    const float z0 = tq_dot(X, T, t, d, k, c);
-    const float z1 = tq_dot(X, T, t, d, k, c + 1);
-    const uint32_t m = max(abs_bits(z0), abs_bits(z1));
-    if (m) atomicMax(amax_ws + t, m);
+    const int64_t step = static_cast<int64_t>(gridDim.x) * kTqThreads;
+    for (int64_t u = static_cast<int64_t>(blockIdx.x) * kTqThreads + threadIdx.x; u < n * pairs; u += step) {
+        const int64_t t = u / pairs;
+        const int64_t c = 2 * (u - t * pairs);
+        const float z0 = tq_dot(X, T, t, d, k, c);
+        const float z1 = tq_dot(X, T, t, d, k, c + 1);
+        const uint32_t m = max(abs_bits(z0), abs_bits(z1));
+        if (m) atomicMax(amax_ws + t, m);
+    }
 }
 
 template <typename XT, typename TT, int QM>
@@ -154,24 +155,25 @@ __global__ __launch_bounds__(kTqThreads) void tq_generic_quant_kernel(
     const uint32_t* __restrict__ amax_ws, uint8_t* __restrict__ codes, float* __restrict__ s_x) {
     constexpr float qmax = static_cast<float>(QM);
     const int64_t pairs = d / 2;
-    const int64_t u = static_cast<int64_t>(blockIdx.x) * kTqThreads + threadIdx.x;
-    if (u >= n * pairs) return;
-    const int64_t t = u / pairs;
-    const int64_t cp = u - t * pairs;
-    const float amax = __uint_as_float(amax_ws[t]);
-    if (cp == 0) s_x[t] = __fdiv_rn(amax, qmax);
-    int q0 = 0, q1 = 0;
-    if (amax > 0.0f) {
-        const float inv = __fdiv_rn(qmax, amax);
-        q0 = quant_code<QM>(tq_dot(X, T, t, d, k, 2 * cp), inv);
-        q1 = quant_code<QM>(tq_dot(X, T, t, d, k, 2 * cp + 1), inv);
-    }
-    if constexpr (QM == 7) {
-        codes[t * pairs + cp] = static_cast<uint8_t>((q0 & 0xF) | ((q1 & 0xF) << 4));
-    } else {
-        // one int8 per code: the pair is two consecutive bytes
-        *reinterpret_cast<uint16_t*>(codes + t * d + 2 * cp) =
-            static_cast<uint16_t>((q0 & 0xFF) | ((q1 & 0xFF) << 8));
+    const int64_t step = static_cast<int64_t>(gridDim.x) * kTqThreads;
+    for (int64_t u = static_cast<int64_t>(blockIdx.x) * kTqThreads + threadIdx.x; u < n * pairs; u += step) {
+        const int64_t t = u / pairs;
+        const int64_t cp = u - t * pairs;
+        const float amax = __uint_as_float(amax_ws[t]);
+        if (cp == 0) s_x[t] = __fdiv_rn(amax, qmax);
+        int q0 = 0, q1 = 0;
+        if (amax > 0.0f) {
+            const float inv = __fdiv_rn(qmax, amax);
+            q0 = quant_code<QM>(tq_dot(X, T, t, d, k, 2 * cp), inv);
+            q1 = quant_code<QM>(tq_dot(X, T, t, d, k, 2 * cp + 1), inv);
+        }
+        if constexpr (QM == 7) {
+            codes[t * pairs + cp] = static_cast<uint8_t>((q0 & 0xF) | ((q1 & 0xF) << 4));
+        } else {
+            // one int8 per code: the pair is two consecutive bytes
+            *reinterpret_cast<uint16_t*>(codes + t * d + 2 * cp) =
+                static_cast<uint16_t>((q0 & 0xFF) | ((q1 & 0xFF) << 8));
+        }
     }
 }
 
@@ -180,14 +182,15 @@ __global__ __launch_bounds__(kTqThreads) void tq_generic_minmax_kernel(
     const XT* __restrict__ X, const TT* __restrict__ T, int64_t n, int64_t d, int64_t k,
     uint32_t* __restrict__ ws) {
     const int64_t pairs = d / 2;
-    const int64_t u = static_cast<int64_t>(blockIdx.x) * kTqThreads + threadIdx.x;
-    if (u >= n * pairs) return;
-    const int64_t t = u / pairs;
-    const int64_t c = 2 * (u - t * pairs);
-    const uint32_t k0 = fkey(tq_dot(X, T, t, d, k, c));
-    const uint32_t k1 = fkey(tq_dot(X, T, t, d, k, c + 1));
-    atomicMax(ws + max_key(t), max(k0, k1));
-    atomicMax(ws + min_key(n, t), max(~k0, ~k1));
+    const int64_t step = static_cast<int64_t>(gridDim.x) * kTqThreads;
+    for (int64_t u = static_cast<int64_t>(blockIdx.x) * kTqThreads + threadIdx.x; u < n * pairs; u += step) {
+        const int64_t t = u / pairs;
+        const int64_t c = 2 * (u - t * pairs);
+        const uint32_t k0 = fkey(tq_dot(X, T, t, d, k, c));
+        const uint32_t k1 = fkey(tq_dot(X, T, t, d, k, c + 1));
+        atomicMax(ws + max_key(t), max(k0, k1));
+        atomicMax(ws + min_key(n, t), max(~k0, ~k1));
+    }
 }
 
 template <typename XT, typename TT>
@@ -196,19 +199,27 @@ __global__ __launch_bounds__(kTqThreads) void tq_generic_quant_asym_kernel(
     const uint32_t* __restrict__ ws, uint8_t* __restrict__ codes, float* __restrict__ s_x,
     float* __restrict__ zmin_x) {
     const int64_t pairs = d / 2;
-    const int64_t u = static_cast<int64_t>(blockIdx.x) * kTqThreads + threadIdx.x;
-    if (u >= n * pairs) return;
-    const int64_t t = u / pairs;
-    const int64_t cp = u - t * pairs;
-    float zmin, s, inv;
-    asym_scale(ws[max_key(t)], ws[min_key(n, t)], zmin, s, inv);
-    if (cp == 0) {
-        s_x[t] = s;
-        zmin_x[t] = zmin;
+    const int64_t step = static_cast<int64_t>(gridDim.x) * kTqThreads;
+    for (int64_t u = static_cast<int64_t>(blockIdx.x) * kTqThreads + threadIdx.x; u < n * pairs; u += step) {
+        const int64_t t = u / pairs;
+        const int64_t cp = u - t * pairs;
+        float zmin, s, inv;
+        asym_scale(ws[max_key(t)], ws[min_key(n, t)], zmin, s, inv);
+        if (cp == 0) {
+            s_x[t] = s;
+            zmin_x[t] = zmin;
+        }
+        const int q0 = asym_code(tq_dot(X, T, t, d, k, 2 * cp), zmin, inv);
+        const int q1 = asym_code(tq_dot(X, T, t, d, k, 2 * cp + 1), zmin, inv);
+        codes[t * pairs + cp] = static_cast<uint8_t>((q0 & 0xF) | ((q1 & 0xF) << 4));
     }
-    const int q0 = asym_code(tq_dot(X, T, t, d, k, 2 * cp), zmin, inv);
-    const int q1 = asym_code(tq_dot(X, T, t, d, k, 2 * cp + 1), zmin, inv);
-    codes[t * pairs + cp] = static_cast<uint8_t>((q0 & 0xF) | ((q1 & 0xF) << 4));
+}
+
+// One channel pair per thread, as long as that is fewer threads than a launch
+// can have (2^32).
+static int64_t tq_generic_grid(int64_t n, int64_t d) {
+    const int64_t blocks = (n * (d / 2) + kTqThreads - 1) / kTqThreads;
+    return blocks < (int64_t{1} << 23) ? blocks : int64_t{1} << 23;
 }
 
 // ---------------------------------------------------------- whole rows
@@ -2341,8 +2352,7 @@ hipError_t launch_tq_generic(const XT* X, int64_t n, int64_t d, const TT* T, int
         return launch_tq_rows<QM, false>(X, n, d, T, k, codes, s_x, nullptr, stream);
     hipError_t err = launch_fill_zero(ws, n, stream);
     if (err != hipSuccess) return err;
-    const int64_t units = n * (d / 2);
-    const int64_t grid = (units + kTqThreads - 1) / kTqThreads;
+    const int64_t grid = tq_generic_grid(n, d);
     hipLaunchKernelGGL((tq_generic_amax_kernel<XT, TT>), dim3(static_cast<uint32_t>(grid)),
                        dim3(kTqThreads), 0, stream, X, T, n, d, k, ws);
     err = hipGetLastError();
@@ -2436,8 +2446,7 @@ static hipError_t launch_tq_generic_asym(const XT* X, int64_t n, int64_t d, cons
         return launch_tq_rows<7, true>(X, n, d, T, k, codes, s_x, zmin_x, stream);
     hipError_t err = launch_fill_zero(ws, 4 * n, stream);
     if (err != hipSuccess) return err;
-    const int64_t units = n * (d / 2);
-    const int64_t grid = (units + kTqThreads - 1) / kTqThreads;
+    const int64_t grid = tq_generic_grid(n, d);
     hipLaunchKernelGGL((tq_generic_minmax_kernel<XT, TT>), dim3(static_cast<uint32_t>(grid)),
                        dim3(kTqThreads), 0, stream, X, T, n, d, k, ws);
     err = hipGetLastError();

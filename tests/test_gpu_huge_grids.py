@@ -39,12 +39,15 @@ def test_second_moments_of_rows_beyond_32_bit_offsets():
         assert err.max().item() <= 2.0 ** -24 * 1.001
 
 
+# whole rows, and channel pairs on the vector ALU
+@pytest.mark.parametrize("n,d,k,x_dtype,border", [((1 << 26) + 33, 16, 16, "float32", 1 << 25),
+                                                  (2_089_100, 4112, 16, "bfloat16", 1_044_506)])
 @pytest.mark.parametrize("asym", [False, True])
-def test_whole_rows_of_more_tokens_than_a_launch(asym):
+def test_transform_quant_of_more_threads_than_a_launch(n, d, k, x_dtype, border, asym):
     torch = torch_mod()
-    n, d, k = (1 << 26) + 33, 16, 16
-    say(f"tq rows {n} x {d}, k={k} asym={asym}")
-    X = torch.randn(n, d, dtype=torch.float32, device="cuda", generator=torch.Generator("cuda").manual_seed(3))
+    say(f"tq {n} x {d}, k={k} asym={asym}")
+    X = torch.randn(n, d, dtype=getattr(torch, x_dtype), device="cuda",
+                    generator=torch.Generator("cuda").manual_seed(3))
     T = dev(_rand_T(d, k, seed=4), "f32")
 
     def call(x):
@@ -61,7 +64,7 @@ def test_whole_rows_of_more_tokens_than_a_launch(asym):
 
     whole = call(X)
     # around the launches' borders and at both ends, against calls of their own
-    for lo in (0, (1 << 25) - 16, n - 50):
+    for lo in (0, border - 16, n - 50):
         part = call(X[lo:lo + 50].clone())
         for a, b in zip(part, whole):
             assert torch.equal(a, b[lo:lo + 50]), f"tokens {lo} on"
