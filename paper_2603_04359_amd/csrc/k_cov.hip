@@ -34,12 +34,25 @@ constexpr int kCovTK = 32;        // tokens per LDS slab
 
 // Decode a linear index over the upper triangle of a T x T tile grid.
 __device__ __forceinline__ void tri_decode(int64_t idx, int64_t T, int64_t& I, int64_t& J) {
-    // row i starts at i (2 T + 1 - i) / 2: the root of that quadratic, put right
-    // where rounding moved it (walking the rows took a microsecond at T = 64)
-    const double b = static_cast<double>(2 * T + 1);
-    int64_t i = static_cast<int64_t>((b - __builtin_sqrt(b * b - 8.0 * static_cast<double>(idx))) * 0.5);
+    int64_t i = 0;
+    while (idx >= T - i) {
+        idx -= T - i;
+        ++i;
+    }
+    I = i;
+    J = i + idx;
+}
+// The same for grids of many rows (walking them took a microsecond at T = 64):
+// row i starts at i (2 T + 1 - i) / 2, so i is the root of that quadratic, put
+// right where rounding moved it.
+__device__ __forceinline__ void tri_decode_many(int64_t idx, int64_t T, int64_t& I, int64_t& J) {
+    int64_t i = 0;
     auto start = [&](int64_t r) { return r * (2 * T + 1 - r) / 2; };
-    while (start(i) > idx) --i;
+    if (T > 8) {
+        const float b = static_cast<float>(2 * T + 1);
+        i = static_cast<int64_t>((b - __builtin_sqrtf(fmaxf(b * b - 8.0f * static_cast<float>(idx), 0.0f))) * 0.5f);
+        while (start(i) > idx) --i;
+    }
     while (start(i + 1) <= idx) ++i;
     I = i;
     J = i + (idx - start(i));
@@ -52,13 +65,15 @@ struct CovTile {
     int64_t base;     // offset of that matrix inside acc
 };
 
+template <bool MANY>
 __device__ __forceinline__ CovTile cov_tile(int64_t work, int tile, int64_t d, int mode,
                                             int64_t k) {
     CovTile c;
     if (mode == CAT_COV_FULL) {
         const int64_t T = (d + tile - 1) / tile;
         int64_t I, J;
-        tri_decode(work, T, I, J);
+        if constexpr (MANY) tri_decode_many(work, T, I, J);
+        else tri_decode(work, T, I, J);
         c.colbase = 0;
         c.dim = d;
         c.I0 = I * tile;
@@ -69,7 +84,8 @@ __device__ __forceinline__ CovTile cov_tile(int64_t work, int tile, int64_t d, i
         const int64_t per = T * (T + 1) / 2;
         const int64_t b = work / per;
         int64_t I, J;
-        tri_decode(work % per, T, I, J);
+        if constexpr (MANY) tri_decode_many(work % per, T, I, J);
+        else tri_decode(work % per, T, I, J);
         c.colbase = b * k;
         c.dim = k;
         c.I0 = I * tile;
@@ -92,7 +108,7 @@ __global__ __launch_bounds__(kCovThreads) void cov_mfma_kernel(const uint16_t* _
     constexpr int TASKS = 2 * (TILE / 2) * UN;  // (channel pair, token group) x 2 operands
     __shared__ u32x4 lds[2][2][TILE * UN];
 
-    const CovTile ct = cov_tile(blockIdx.x, TILE, d, mode, k);
+    const CovTile ct = cov_tile<false>(blockIdx.x, TILE, d, mode, k);
     const bool diag = ct.I0 == ct.J0;
     const int tid = threadIdx.x;
     const int lane = tid & (kWave - 1);
@@ -273,7 +289,7 @@ __global__ __launch_bounds__(kCovFThreads, UN == 4 ? 6 : 2) void cov_f64_kernel(
         ct.I0 = ct.J0 = 0;
         ct.base = ct.colbase * k;
     } else {
-        ct = cov_tile(work, TILE, d, mode, k);
+        ct = cov_tile<true>(work, TILE, d, mode, k);
     }
     const bool diag = ct.I0 == ct.J0;
     const int tid = threadIdx.x;
