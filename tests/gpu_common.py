@@ -44,7 +44,8 @@ def dev(a, dtype):
 
 
 def gemm_tile_rows(n, d_out):
-    """Token rows per tile the integer GEMMs launch with on this device:
+    """Token rows per large tile the integer GEMMs take on this device, where
+    the launcher does not pick the small tiles (few tokens or outputs):
     128 when 256-row tiles would leave CUs idle and 128-row ones take no
     more rounds of the one-workgroup-per-CU grid, else 256."""
     torch = torch_mod()
@@ -55,8 +56,8 @@ def gemm_tile_rows(n, d_out):
 
 
 def check_tile_rows(n, d_out, rows):
-    """On a 256-CU MI355X, asserts that the case runs on the expected tile
-    height (elsewhere the rule may pick another, and the case still runs)."""
+    """On a 256-CU MI355X, asserts the large tiles' height for the case; it
+    does not see whether the small tiles take it instead (elsewhere the rule may pick another, and the case still runs)."""
     torch = torch_mod()
     if torch.cuda.get_device_properties(0).multi_processor_count == 256:
         assert gemm_tile_rows(n, d_out) == rows

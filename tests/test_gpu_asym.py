@@ -55,8 +55,9 @@ def _check_asym(q, s, m, X, T, label):
     say(f"  {label}: codes {q.size}, tie mismatches {nm}")
 
 
-# bf16 group kernels (k <= 256, d a multiple of 256), ring kernels (k = 512,
-# and k = 128 at d = 640) and vector-ALU kernels (fp32)
+# bf16 single pass (d = 4096, k = 128), wide and group kernels (d a multiple of
+# 256), ring kernels (k = 128 at d = 640, k = 512 at few tokens) and whole rows
+# (fp32)
 @pytest.mark.parametrize("d,k,n,x_dtype,t_dtype", [
     (4096, 128, 300, "bf16", "bf16"), (1024, 256, 129, "bf16", "bf16"),
     (1024, 512, 65, "bf16", "bf16"), (512, 64, 70, "bf16", "bf16"), (256, 32, 33, "f32", "f32"),

@@ -95,7 +95,7 @@ TILE_HEIGHT_CASES = [
     (4352, 1056, 3840, False, 256),   # 255 tiles of 256 rows: one CU idle, stays at 256
     (1900, 4160, 3000, True, 128),    # 96 tiles of 256 rows become 180 of 128, ragged
     (2048, 4096, 4096, False, 128),   # the attention-projection shape, full tiles
-    (129, 96, 8000, False, 128),      # a last 128-row panel holding one row
+    (129, 96, 8000, False, 128),      # few tokens: the small tiles (a one-row 128 panel is test_gpu_large_tile_gemm's)
 ]
 
 
@@ -403,10 +403,10 @@ def test_transform_quant_k128_other_widths(d, n):
     (640, 128, 300), (384, 64, 129), (2048, 512, 1000), (4096, 512, 33),
 ])
 def test_transform_quant_two_pass_shapes(d, k, n):
-    # bf16 two-pass paths: 256-channel group kernels (k <= 256, d a multiple
-    # of 256; the mlp_down width with a ragged last tile), the ring and
-    # small-block kernels they leave to (d = 640, 384), and k = 512 ring
-    # workgroups paired on one XCD
+    # bf16 two-pass paths: wide and group kernels (k <= 256, d a multiple of
+    # 256; the mlp_down width with a ragged last tile), the ring and
+    # small-block kernels they leave to (d = 640, 384), and k = 512 on the wide
+    # and, at few tokens, the ring kernel
     say(f"tq two-pass d={d} k={k} n={n}")
     rng = np.random.default_rng(3 * d + k + n)
     X = o.round_storage(rng.standard_normal((n, d)) * np.exp(rng.standard_normal(d)), "bf16")
@@ -498,9 +498,8 @@ def test_transform_quant_workspace_reuse_across_paths():
         codes = torch.empty((n, d // 2), dtype=torch.uint8, device="cuda")
         s_x = torch.empty(n, dtype=torch.float32, device="cuda")
         # the single-pass kernel's bounded waits record a timeout in the word
-        # at cat_transform_quant_flag_offset of the call's shape (wider calls
-        # put exchange words where a narrower call's flag sits, so each call
-        # clears and checks its own)
+        # at cat_transform_quant_flag_offset of the call's shape; each call
+        # clears and checks its own
         fo = cat.cat_transform_quant_flag_offset(n, d, 128)
         ws[fo:fo + 4].zero_()
         cat.cat_transform_quant(dev(X, "bf16"), dev(T, "bf16"), 128, codes, s_x, ws)

@@ -39,9 +39,9 @@ def _rand_T(d, k, seed, dtype):
 
 
 # (d, k, n, x_dtype, t_dtype): the single-pass kernel (d = 2048, 4096,
-# 8192, k = 128, bf16), the two-pass group kernels (k <= 256 with d a multiple of 256),
-# the ring kernels (k = 512; k = 128 at d = 640), the small-block MFMA
-# kernel (k = 64 at d = 384) and the vector-ALU kernels (fp32, k = 16)
+# 8192, k = 128, bf16), the two-pass wide and group kernels (d a multiple of 256),
+# the ring kernels (k = 512 at few tokens; k = 128 at d = 640), the small-block
+# MFMA kernel (k = 64 at d = 384) and whole rows (fp32, k = 16)
 PATHS = [(4096, 128, 300, "bf16", "bf16"), (8192, 128, 130, "bf16", "bf16"),
          (2048, 128, 97, "bf16", "bf16"), (1024, 128, 257, "bf16", "bf16"),
          (1024, 256, 129, "bf16", "bf16"), (1024, 512, 65, "bf16", "bf16"),
