@@ -13,16 +13,16 @@
 // the X stream, not by the matrix cores).  The design notes are at that
 // kernel.
 //
-// Other small bf16 matrices (64 to 255 channels, or widths that are not a
-// multiple of 32) run cov_mfma_kernel: one workgroup per 128 x 128 (or
+// Other bf16 matrices of 64 channels and more (64 to 255, or widths that are
+// even but not a multiple of 32) run cov_mfma_kernel: one workgroup per 128 x 128 (or
 // 64 x 64) upper-triangle tile looping over all tokens; each 32-token slab
 // is transposed on its way into LDS (4-byte loads of channel pairs split
 // with v_perm into 16-byte runs of 8 tokens per channel).  Partial sums
 // stay in registers for at most 4096 tokens and are then added into acc by
 // the tile's owner together with the transpose.
 //
-// fp32 inputs and blocks smaller than 64 use cov_f64_kernel: fp64 MFMA, small
-// tiles, a tile's tokens split over the waves of its workgroup.
+// fp32 inputs, odd widths and blocks smaller than 64 use cov_f64_kernel: fp64
+// MFMA, small tiles, a tile's tokens split over the waves of its workgroup.
 #include "device_common.h"
 #include "kernels.h"
 
@@ -245,8 +245,8 @@ __global__ __launch_bounds__(kCovThreads) void cov_mfma_kernel(const uint16_t* _
 // rate at many tokens, at few by the latency of a tile (load, reduce, update
 // acc) and how many tiles a CU holds at once, so tiles are small and registers
 // are kept few.  Against 64 x 64 vector-ALU tiles walking all tokens: 512
-// tokens of 8 blocks of 32 channels 66 -> 6.4 us; 2048 x 512, whole matrix, 368
-// -> 22 us; 8192 x 1024 1527 -> 215 us; 1 x 2048 18.6 -> 14.9.
+// tokens of 8 blocks of 32 channels 67 -> 6 us; 2048 x 512, whole matrix, 421
+// -> 25 us; 8192 x 1024 1528 -> 217 us; 1 x 2048 18.7 -> 15.
 typedef double f64x4 __attribute__((ext_vector_type(4)));
 constexpr int kCovFWaves = 8;
 constexpr int kCovFThreads = kCovFWaves * kWave;

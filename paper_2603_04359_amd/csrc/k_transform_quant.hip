@@ -1726,10 +1726,10 @@ hipError_t launch_tq_group(const uint16_t* X, int64_t n, int64_t d, const uint16
 // leave as 8 bytes per lane, 128 contiguous bytes per token over the 8 waves.
 // Against the kernels that ran these cases before (group kernel up to 256, ring
 // kernel at 512), whole calls, INT4:
-//   16384 x 8192, k = 512   340 -> 243 us (passes 108 and 121 us at best)
-//   4096 x 4096, k = 512     55 -> 40 us
-//   4096 x 14336, k = 256    78 -> 73 us, asymmetric 99 -> 83; 8192 tokens 137
-//                           and 136; 300 x 4096 16.5 -> 11.3 us
+//   16384 x 8192, k = 512   326 -> 242 us (passes 108 and 121 us at best)
+//   4096 x 4096, k = 512     56 -> 39 us (8-bit)
+//   4096 x 14336, k = 256    78 -> 73 us, asymmetric 99 -> 83; 8192 tokens 145
+//                           -> 140; 300 x 4096 16.1 -> 11.2 us
 //   4096 x 1280, k = 128    16.1 -> 12.3 us
 // workspace offsets (defined with its layout below)
 constexpr size_t kTqHeadBytes = 4096;
@@ -1790,9 +1790,9 @@ __global__ __launch_bounds__(kTwThreads, 1) void tq_wide_kernel(
     const int l32 = lane & 31, h = lane >> 5;
     // Pass 2 walks its tiles from the last to the first: pass 1 left the end of
     // X in the last-level cache (256 MiB), and walking forward would evict it
-    // before reading it.  Calls with pass 2 forward and back: 16384 x 8192, k =
-    // 512 263 -> 253 us, k = 256 162 -> 149, k = 64 (group kernel) 112 -> 104;
-    // 8192 x 14336, k = 256, 8 bits 144 -> 138; calls whose X is small the same.
+    // before reading it.  Calls with pass 2 forward and back: 24000 x 6144, k =
+    // 256 177 -> 172 us; group kernel, k = 64, 10000 x 14336 138 -> 120, 8192 x
+    // 14336 106 -> 97, 4096 x 6144 27.0 -> 25.1; X of 170 to 200 MB the same.
     auto tile0 = [&](int64_t it) { return (r0 + (QUANT ? nt - 1 - it : it) * R) * kTwTT; };
     const int64_t ch = b * KT + half * kTwRows + wave * 32;   // this wave's first channel
     const int xo = (wave * 32 % KT) / K * (K / 8);  // first unit of its block in a tile row
