@@ -57,7 +57,8 @@ def gemm_tile_rows(n, d_out):
 
 def check_tile_rows(n, d_out, rows):
     """On a 256-CU MI355X, asserts the large tiles' height for the case; it
-    does not see whether the small tiles take it instead (elsewhere the rule may pick another, and the case still runs)."""
+    does not see whether the small tiles take it instead (elsewhere the rule
+    may pick another height, and the case still runs)."""
     torch = torch_mod()
     if torch.cuda.get_device_properties(0).multi_processor_count == 256:
         assert gemm_tile_rows(n, d_out) == rows
